@@ -30,7 +30,8 @@ STORE_BYTES = {"f64": 8, "f32": 4, "f16": 2, "bf16": 2}
 _CSRC = os.path.join("paper_2307_11752_amd", "csrc")
 KERNEL_SOURCES = {
     "lattice": [os.path.join(_CSRC, n) for n in ("lbm.hip", "lattice.hpp", "fluid_path.hpp",
-                                                  "handle.hpp")] + ["include/lbm.h"],
+                                                  "handle.hpp", "pair.hip", "pair.hpp",
+                                                  "pair_path.hpp", "pair_plan.hip")] + ["include/lbm.h"],
     "batch": [os.path.join(_CSRC, n) for n in ("batch.hip", "lattice.hpp", "fluid_path.hpp",
                                                 "handle.hpp")] + ["include/lbm.h"],
     "porous": [os.path.join(_CSRC, n) for n in ("adjoint.hip", "lattice.hpp", "handle.hpp")]

@@ -94,7 +94,13 @@ typedef enum {
  * propagation phase, so read populations with lbm_get_populations.
  * aux_bytes: per-cell link masks plus device scratch (the partial sums of
  * lbm_totals and the staging of lbm_moments: 32 bytes per cell, at least
- * 64 KiB and at most 1 MiB).  Host-only; needs no GPU. */
+ * 64 KiB and at most 1 MiB), plus, for populations below 2^32 bytes, a second
+ * population buffer of pop_bytes, through which runs of four and more steps
+ * advance two steps per pass (the state is in dev_pop again when the run
+ * ends).  lbm_lattice_create also takes an aux buffer without that last part
+ * (9 bytes per cell plus the scratch, each part rounded up to 256 bytes): the
+ * lattice then takes every step in place.  The results are the same bit for
+ * bit.  Host-only; needs no GPU. */
 lbm_status lbm_required_bytes(lbm_descriptor d, int nx, int ny, int nz, lbm_storage s,
                               size_t* pop_bytes, size_t* aux_bytes);
 
@@ -102,7 +108,8 @@ lbm_status lbm_required_bytes(lbm_descriptor d, int nx, int ny, int nz, lbm_stor
  * (omega = 1/tau, collision equation of the guide's introduction); it must be
  * > 1/2 (the guide requires a relaxation time greater than 0.5), or +INFINITY
  * for omega = 0 (pure streaming, used for bit-exact tests).  dev_pop/dev_aux
- * must hold at least lbm_required_bytes() and be 256-byte aligned.  hip_stream
+ * must hold at least lbm_required_bytes() (dev_aux: with or without the second
+ * population buffer) and be 256-byte aligned.  hip_stream
  * is a hipStream_t (NULL = null stream).  The lattice starts with no geometry,
  * g = 0 and u_w = 0.  Host-side argument checks run before any HIP call. */
 lbm_status lbm_lattice_create(lbm_lattice** out, lbm_descriptor d, int nx, int ny, int nz,

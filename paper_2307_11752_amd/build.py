@@ -5,12 +5,15 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SRC = [os.path.join(HERE, "csrc", n) for n in ("lbm.hip", "batch.hip", "adjoint.hip")]
-DEPS = SRC + [os.path.join(HERE, "csrc", n) for n in ("lattice.hpp", "handle.hpp", "fluid_path.hpp")] \
-    + [os.path.join(ROOT, "include", "lbm.h")]
+CSRC = os.path.join(HERE, "csrc")
+# (object name, source, extra flags): pair.hip is compiled once per storage type
+UNITS = [(n, os.path.join(CSRC, n + ".hip"), ()) for n in ("lbm", "batch", "adjoint", "pair_plan")] \
+    + [(f"pair_{t}", os.path.join(CSRC, "pair.hip"), (f"-DLBM_PAIR_STORAGE={k}",))
+       for k, t in enumerate(("f64", "f32", "f16", "bf16"))]
 LIB = os.path.join(HERE, "liblbm_hip.so")
 ARCH = "gfx950"
 
@@ -22,14 +25,14 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def compile_cmd(out: str, extra=()) -> list:
+def compile_cmd(out: str, src: str, extra=()) -> list:
     return [
-        hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
+        hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-c",
         # packed FP32 instructions stay off in all device code
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
         "-Wall", "-Wno-unused-function",
-        "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc"),
-        *extra, *SRC, "-o", out,
+        "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+        *extra, src, "-o", out,
     ]
 
 
@@ -46,13 +49,23 @@ def diagnostics(output: str) -> str:
 
 
 def build(verbose: bool = False) -> str:
-    tmp = LIB + ".tmp"
-    cmd = compile_cmd(tmp)
+    """Compile every unit (in parallel) and link the library."""
+    objdir = os.path.join(HERE, "_build")
+    os.makedirs(objdir, exist_ok=True)
+    objs = [os.path.join(objdir, name + ".o") for name, _, _ in UNITS]
+    cmds = [compile_cmd(o, src, extra) for o, (_, src, extra) in zip(objs, UNITS)]
     if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    report = diagnostics(res.stdout + res.stderr)
-    if res.returncode != 0:
+        for cmd in cmds:
+            print(" ".join(cmd), flush=True)
+    jobs = int(os.environ.get("MAX_JOBS", 0)) or min(len(cmds), os.cpu_count() or 1, 8)
+    with ThreadPoolExecutor(max_workers=jobs) as pool:
+        results = list(pool.map(lambda c: subprocess.run(c, capture_output=True, text=True), cmds))
+    tmp = LIB + ".tmp"
+    if all(r.returncode == 0 for r in results):
+        results.append(subprocess.run([hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC",
+                                       *objs, "-o", tmp], capture_output=True, text=True))
+    report = diagnostics("".join(r.stdout + r.stderr for r in results))
+    if any(r.returncode != 0 for r in results):
         sys.stderr.write(report)
         raise RuntimeError("hipcc failed building liblbm_hip.so")
     if report.strip():

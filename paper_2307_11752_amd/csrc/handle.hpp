@@ -11,6 +11,7 @@
 
 #include "lattice.hpp"
 #include "lbm.h"
+#include "pair.hpp"
 
 constexpr int RED_BLOCKS = 1024;
 constexpr int RED_THREADS = 256;
@@ -32,11 +33,13 @@ inline size_t scratch_size(size_t N) {
 
 struct AuxLayout {
   size_t link, mov, cls, result, scratch, total;
+  size_t second, total_with_second;  // second population buffer (256-byte aligned)
 };
 
 // Aux buffer of a lattice of N cells with `scratch` bytes of its own scratch
-// (0 for a batch member, which uses the batch's).
-inline AuxLayout aux_layout(size_t N, size_t scratch) {
+// (0 for a batch member, which uses the batch's), and optionally a second
+// population buffer of `second` bytes.
+inline AuxLayout aux_layout(size_t N, size_t scratch, size_t second = 0) {
   AuxLayout a;
   a.link = 0;
   a.mov = align256(a.link + 4 * N);
@@ -44,6 +47,8 @@ inline AuxLayout aux_layout(size_t N, size_t scratch) {
   a.result = align256(a.cls + N);
   a.scratch = align256(a.result + sizeof(double) * RED_FIELDS);
   a.total = align256(a.scratch + scratch);
+  a.second = a.total;
+  a.total_with_second = align256(a.second + second);
   return a;
 }
 
@@ -123,10 +128,17 @@ struct lbm_lattice {
   long long nfluid = 0;
   int bx = 256, nxb = 1;
   int lds_per_cu = 0;  // bytes of LDS per compute unit (occupancy caps)
-  // Replay of a captured run of graph_steps steps (0 = direct launches).  The
-  // graph bakes in the kernel arguments, so any parameter change drops it.
+  int num_cu = 0;
+  // Two steps per pass (pair_path.hpp): passes go from `pop` to `second` and
+  // back, an even number of them at a time, so that the state is always in
+  // `pop` between calls.  Null second: the aux buffer has no room for it.
+  void* second = nullptr;
+  PairPlan pair{};
+  // Replay of captured runs of graph_steps steps (0 = direct launches), one
+  // per propagation phase they start in and parity of their first step.  The
+  // graphs bake in the kernel arguments, so any parameter change drops them.
   int graph_steps = 0;
-  hipGraphExec_t graph = nullptr;
+  hipGraphExec_t graph[4] = {};
   // Non-null for a lattice owned by a batch (lbm_batch_lattice): the batch
   // advances it, and calls that would change what the batch launch assumes
   // are refused.

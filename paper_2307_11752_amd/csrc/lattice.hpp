@@ -204,6 +204,7 @@ struct StepParams {
   T mw[19];     // 6 w_i (c_i . u_w): moving-wall momentum term per unit density
   int has_force;
   int has_moving;
+  int fused_u;  // bit 0: step taken (first of two), bit 1: second of two; see collide
 };
 
 // Velocity i + H (H = (Q - 1) / 2) is the opposite of velocity i for
@@ -229,19 +230,6 @@ __device__ __forceinline__ float reciprocal(float v) {
 }
 __device__ __forceinline__ double reciprocal(double v) { return 1.0 / v; }
 
-// One BGK + Guo collision of a cell held in registers (in place).
-//   rho = base + sum f  (base = p.base when f stores f_i - w_i, else 0;
-//                        p.base = 1 unless the storage holds scaled values)
-//   u   = j/rho + g/2                                  (Guo velocity shift)
-//   feq_i - base*w_i = w_i (sum f + rho (3 c.u + 4.5 (c.u)^2 - 1.5 u.u))
-//   f*_i = f_i + omega (feq_i - f_i) + (1 - omega/2) w_i (3 (c_i - u).F + 9 (c_i.u)(c_i.F))
-// with F = rho g.  Returns rho.
-// Evaluated by opposite pairs (i, i + H): with A = sum f - 1.5 rho u.u, the
-// equilibrium is P + M for velocity i and P - M for its opposite, P = w_i (A +
-// 4.5 rho (c_i.u)^2) and M = 3 w_i rho c_i.u; the Guo source likewise is
-// G_P + G_M and G_P - G_M, G_P = (1 - omega/2) w_i (9 (c_i.u)(c_i.F) - 3 u.F)
-// and G_M = 3 (1 - omega/2) w_i c_i.F.  The relaxation keeps the form
-// f + omega (feq - f), whose rounding is that of the small non-equilibrium part.
 // Compile-time loop: f(integral_constant<int, K>) for K = B .. E-1, so that
 // the velocity components are constants inside the body.
 template <int B, int E, typename F>
@@ -274,6 +262,15 @@ __device__ __forceinline__ T cdot(T x, T y, T z) {
   }
 }
 
+// c.F for F = rho g (Fx .. Fz), its second term fused.
+template <int A, int B, int C, typename T>
+__device__ __forceinline__ T force_dot(T rho, const T (&g)[3], T Fx, T Fy, T Fz) {
+  const T first = A != 0 ? (A > 0 ? Fx : -Fx) : (B != 0 ? (B > 0 ? Fy : -Fy) : (C > 0 ? Fz : -Fz));
+  if constexpr (A != 0 && B != 0) return fma(B > 0 ? rho : -rho, g[1], first);
+  if constexpr ((A != 0 || B != 0) && C != 0) return fma(C > 0 ? rho : -rho, g[2], first);
+  return first;
+}
+
 // acc + s v for a compile-time sign s in {-1, 0, 1}; `first` marks an
 // accumulator that holds nothing yet (it then becomes s v, not 0 + s v).
 template <int Sg, typename T>
@@ -300,14 +297,24 @@ __device__ __forceinline__ void accumulate(T& acc, bool& first, T v) {
 // G_P + G_M and G_P - G_M, G_P = (1 - omega/2) w_i (9 (c_i.u)(c_i.F) - 3 u.F)
 // and G_M = 3 (1 - omega/2) w_i c_i.F.  The relaxation keeps the form
 // f + omega (feq - f), whose rounding is that of the small non-equilibrium part.
+// Every fused multiply-add is written out and contraction is off: left to the
+// compiler, the choice differs from kernel to kernel, and the result of a run
+// would depend on how its steps fall on the kernels (in place, two per pass,
+// batched, replayed).  All of them give the same bits for the same cell.
+// fused_u: u = j/rho + g/2 rounds once, else j/rho rounds before g/2 is added.
+// Large lattices with walls take the former on even steps (StepParams::fused_u,
+// set by the step's number), every other forced step the latter; 16-bit results
+// depend on it, and are those of the library's earlier kernels.
 template <int Q, bool SHIFT, typename T>
-__device__ __forceinline__ T collide(T (&f)[Q], const StepParams<T>& p) {
+__device__ __forceinline__ T collide(T (&f)[Q], const StepParams<T>& p, bool fused_u = false) {
+#pragma clang fp contract(off)
   using V = Vel<Q>;
   constexpr int H = (Q - 1) / 2;
   static_assert(pairs_are_opposite<Q>(), "velocity i + H must be the opposite of velocity i");
   T sf = f[0], jx = T(0), jy = T(0), jz = T(0);
   bool fx = true, fy = true, fz = true;
   static_for<1, H + 1>([&](auto kc) {
+#pragma clang fp contract(off)
     constexpr int k = decltype(kc)::value;
     const T d = f[k] - f[k + H];
     sf += f[k] + f[k + H];
@@ -319,15 +326,17 @@ __device__ __forceinline__ T collide(T (&f)[Q], const StepParams<T>& p) {
   const T inv = reciprocal(rho);
   T ux = jx * inv, uy = jy * inv, uz = V::D == 3 ? jz * inv : T(0);
   if (p.has_force) {
-    ux += T(0.5) * p.g[0];
-    uy += T(0.5) * p.g[1];
-    if (V::D == 3) uz += T(0.5) * p.g[2];
+    const T hx = T(0.5) * p.g[0], hy = T(0.5) * p.g[1], hz = T(0.5) * p.g[2];
+    ux = fused_u ? fma(jx, inv, hx) : ux + hx;
+    uy = fused_u ? fma(jy, inv, hy) : uy + hy;
+    if (V::D == 3) uz = fused_u ? fma(jz, inv, hz) : uz + hz;
   }
-  const T uu = V::D == 3 ? ux * ux + uy * uy + uz * uz : ux * ux + uy * uy;
-  const T A = sf - T(1.5) * rho * uu;
+  const T uu = V::D == 3 ? fma(uz, uz, fma(uy, uy, ux * ux)) : fma(ux, ux, uy * uy);
+  const T A = fma(T(-1.5) * rho, uu, sf);
   const T om = p.omega;
-  f[0] = fma(om, weight<Q, T>(0) * A - f[0], f[0]);
+  f[0] = fma(om, fma(weight<Q, T>(0), A, -f[0]), f[0]);
   static_for<1, H + 1>([&](auto kc) {
+#pragma clang fp contract(off)
     constexpr int k = decltype(kc)::value;
     const T w = weight<Q, T>(k);
     const T cu = cdot<V::cx[k], V::cy[k], V::cz[k]>(ux, uy, uz);
@@ -335,30 +344,39 @@ __device__ __forceinline__ T collide(T (&f)[Q], const StepParams<T>& p) {
     // w multiplies last: a folded constant such as 3 w would carry its own
     // rounding (1/6 is not a binary fraction), a bias the odd part would add
     // to the momentum of every collision
-    const T P = w * fma(T(4.5) * rc, cu, A);
+    const T E = fma(T(4.5) * rc, cu, A);
     const T M = w * (T(3) * rc);
-    f[k] = fma(om, (P + M) - f[k], f[k]);
-    f[k + H] = fma(om, (P - M) - f[k + H], f[k + H]);
+    f[k] = fma(om, fma(w, E, M) - f[k], f[k]);
+    f[k + H] = fma(om, fma(w, E, -M) - f[k + H], f[k + H]);
   });
   // The Guo source is a block of its own behind a uniform branch, so that
   // unforced lattices skip it instead of computing and discarding it.
   if (p.has_force) {
     const T Fx = rho * p.g[0], Fy = rho * p.g[1], Fz = V::D == 3 ? rho * p.g[2] : T(0);
-    const T uF = V::D == 3 ? ux * Fx + uy * Fy + uz * Fz : ux * Fx + uy * Fy;
+    T uF = fma(ux, Fx, uy * Fy);
+    if (V::D == 3) uF = fma(uz, Fz, uF);
     const T kg = p.kguo;
-    f[0] += kg * weight<Q, T>(0) * (T(-3) * uF);
+    const T m3uF = T(-3) * uF;
+    f[0] = fma(kg * weight<Q, T>(0), m3uF, f[0]);
     static_for<1, H + 1>([&](auto kc) {
+#pragma clang fp contract(off)
       constexpr int k = decltype(kc)::value;
       const T kw = kg * weight<Q, T>(k);
       const T cu = cdot<V::cx[k], V::cy[k], V::cz[k]>(ux, uy, uz);
-      const T cF = cdot<V::cx[k], V::cy[k], V::cz[k]>(Fx, Fy, Fz);
-      const T GP = kw * fma(T(9) * cu, cF, T(-3) * uF);
+      const T cF = force_dot<V::cx[k], V::cy[k], V::cz[k]>(rho, p.g, Fx, Fy, Fz);
+      const T GE = fma(T(9) * cu, cF, m3uF);
       const T GM = kw * (T(3) * cF);
-      f[k] += GP + GM;
-      f[k + H] += GP - GM;
+      f[k] += fma(kw, GE, GM);
+      f[k + H] += fma(kw, GE, -GM);
     });
   }
   return rho;
+}
+
+// Population v reflected by a moving wall, mw = 6 w_i (c_i . u_w).
+template <typename T>
+__device__ __forceinline__ T reflect_moving(T v, T rho, T mw) {
+  return fma(-rho, mw, v);
 }
 
 // ---------------------------------------------------------------------------

@@ -169,12 +169,12 @@ __global__ void __launch_bounds__(256)
     }
   }
 
-  const T rho = collide<Q, SHIFT, T>(f, p);
+  const T rho = collide<Q, SHIFT, T>(f, p, MASKED && (p.fused_u & 1));
 
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     T v = f[i];
-    if (MASKED && i > 0 && ((mv >> (i - 1)) & 1u)) v -= rho * p.mw[i];
+    if (MASKED && i > 0 && ((mv >> (i - 1)) & 1u)) v = reflect_moving(v, rho, p.mw[i]);
     uint32_t off;
     if (PHASE == 0) {
       off = L.at(V::opp[i], idx);
@@ -309,11 +309,11 @@ __global__ void __launch_bounds__(256)
     T f[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) f[i] = Store<S>::cvt(sv[i][k]);
-    const T rho = collide<Q, SHIFT, T>(f, p);
+    const T rho = collide<Q, SHIFT, T>(f, p, p.fused_u & 1);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       T v = f[i];
-      if (i > 0 && ((mv >> (i - 1)) & 1u)) v -= rho * p.mw[i];
+      if (i > 0 && ((mv >> (i - 1)) & 1u)) v = reflect_moving(v, rho, p.mw[i]);
       sv[V::opp[i]][k] = Store<S>::pack(v);
     }
   }
@@ -562,11 +562,14 @@ lbm_status fail(lbm_lattice* h, lbm_status st, const std::string& msg) {
 }
 
 void drop_graph(lbm_lattice* h) {
-  if (h->graph) {
-    // a replay may still be running on the lattice's stream
-    (void)hipStreamSynchronize(h->stream);
-    (void)hipGraphExecDestroy(h->graph);
-    h->graph = nullptr;
+  bool any = false;
+  for (hipGraphExec_t g : h->graph) any |= g != nullptr;
+  if (!any) return;
+  // a replay may still be running on the lattice's stream
+  (void)hipStreamSynchronize(h->stream);
+  for (hipGraphExec_t& g : h->graph) {
+    if (g) (void)hipGraphExecDestroy(g);
+    g = nullptr;
   }
 }
 
@@ -662,8 +665,15 @@ lbm_status check_dims(lbm_descriptor d, int nx, int ny, int nz, std::string* why
   return LBM_OK;
 }
 
+// Lattices with walls whose in-place local phase takes the flat kernel
+// (step_p0_masked_kernel): small ones are latency-bound, the per-cell kernel,
+// with more and smaller blocks, is faster there.
+inline bool flat_masked(const lbm_lattice* h) {
+  return h->N % (8 / storage_bytes(h->storage)) == 0 && h->N >= 65536;
+}
+
 template <typename T>
-StepParams<T> make_params(const lbm_lattice* h) {
+StepParams<T> make_params(const lbm_lattice* h, long long step) {
   StepParams<T> p{};
   p.omega = (T)h->omega;
   p.kguo = (T)(1.0 - 0.5 * h->omega);
@@ -685,6 +695,8 @@ StepParams<T> make_params(const lbm_lattice* h) {
     uwdot += fabs(cu);
   }
   p.has_moving = (h->has_moving_cells && uwdot != 0.0) ? 1 : 0;
+  // `step`: the number of the (first) step taken since the initialisation
+  if (!h->all_fluid && flat_masked(h)) p.fused_u = (step & 1) ? 2 : 1;
   return p;
 }
 
@@ -735,8 +747,8 @@ struct Ops {
     }
   }
 
-  static void step(lbm_lattice* h, int phase) {
-    StepParams<T> p = make_params<T>(h);
+  static void step(lbm_lattice* h, int phase, long long number) {
+    StepParams<T> p = make_params<T>(h, number);
     p.base = (T)Store<S>::unit;
     S* pop = (S*)h->pop;
     const uint32_t* link = (const uint32_t*)(h->aux + h->lay.link);
@@ -777,9 +789,8 @@ struct Ops {
                            occupancy_lds(h, rpb * tpr <= 128 ? 4 : 3, lds), h->stream, pop, h->nx,
                            h->ny, h->nz, L, tpr, rpb, p);
       }
-    } else if (!h->all_fluid && h->N % C == 0 && h->N >= 65536 && phase == 0) {
-      // (small lattices are latency-bound: the per-cell kernel below, with
-      // more and smaller blocks, is faster there).  Six blocks per CU for
+    } else if (!h->all_fluid && flat_masked(h) && phase == 0) {
+      // Six blocks per CU for
       // 4- and 8-byte storage (measured); 16-bit storage gains nothing from a cap.
       const unsigned threads = 128;
       const unsigned nb = (unsigned)((h->N / C + threads - 1) / threads);
@@ -797,6 +808,15 @@ struct Ops {
         hipLaunchKernelGGL((step_kernel<Q, S, SHIFT, 1, true>), grid, block, 0, h->stream, pop,
                            link, mov, h->nx, h->ny, h->nz, L, h->nxb, p);
     }
+  }
+
+  // Two steps from src (natural form: entry) to dst.
+  static void pair(lbm_lattice* h, const void* src, void* dst, bool entry, long long number) {
+    StepParams<T> p = make_params<T>(h, number);
+    p.base = (T)Store<S>::unit;
+    const PairLaunch a{&h->pair, src, dst, (const uint32_t*)(h->aux + h->lay.link),
+                       (const uint32_t*)(h->aux + h->lay.mov), entry ? 1 : 0, h->stream};
+    lbm_detail::launch_pair<S>(Q, SHIFT, !h->all_fluid, a, p);
   }
 
   static unsigned blocks(size_t N) {
@@ -845,7 +865,8 @@ struct Ops {
 };
 
 struct OpTable {
-  void (*step)(lbm_lattice*, int);
+  void (*step)(lbm_lattice*, int, long long);
+  void (*pair)(lbm_lattice*, const void*, void*, bool, long long);
   void (*get_pop)(lbm_lattice*, double*);
   void (*set_pop)(lbm_lattice*, const double*);
   void (*init_eq)(lbm_lattice*, const double*, const double*);
@@ -857,7 +878,7 @@ struct OpTable {
 template <int Q, typename S, bool SHIFT>
 OpTable table() {
   using O = Ops<Q, S, SHIFT>;
-  return OpTable{O::step, O::get_pop, O::set_pop, O::init_eq, O::moments_f64, O::moments_f32,
+  return OpTable{O::step, O::pair, O::get_pop, O::set_pop, O::init_eq, O::moments_f64, O::moments_f32,
                  O::totals};
 }
 
@@ -963,44 +984,58 @@ lbm_status reduce_totals(lbm_lattice* h, double* partials, double* result, doubl
   return LBM_OK;
 }
 
+// Launch n steps from propagation phase `phase`, the first of them number
+// `number` since the initialisation; returns the phase they end in.  Whole
+// fours of steps run as two passes of two steps, there and back between the
+// two population buffers (leaving phase 1), the others one by one in place.
+int launch_steps(lbm_lattice* h, const OpTable& t, int n, int phase, long long number) {
+  if (h->pair.use && h->second) {
+    for (; n >= 4; n -= 4, number += 4) {
+      t.pair(h, h->pop, h->second, phase == 0, number);
+      t.pair(h, h->second, h->pop, false, number + 2);
+      phase = 1;
+    }
+  }
+  for (; n > 0; --n, ++number) {
+    t.step(h, phase, number);
+    phase ^= 1;
+  }
+  return phase;
+}
+
 // Enqueue n steps on the lattice's stream (graph replays where set up),
 // updating the phase launch by launch.  Returns LBM_ERR_HIP on a HIP failure.
 lbm_status enqueue_steps(lbm_lattice* h, int n) {
   const OpTable t = ops(h);
   int left = n;
-  if (h->graph_steps > 0 && n >= h->graph_steps) {
-    // The captured run starts in phase 0 and has an even length, so it can be
-    // replayed whenever the lattice is in phase 0.
-    if (h->phase != 0) {
-      t.step(h, 1);
-      h->phase = 0;
-      --left;
-    }
-    if (!h->graph && left >= h->graph_steps) {
+  while (h->graph_steps > 0 && left >= h->graph_steps) {
+    // the phase a run of this length ends in (its length is even: the phase it
+    // starts in, unless it takes passes of two steps)
+    const bool pairs = h->pair.use && h->second && h->graph_steps >= 4;
+    const int end = pairs ? 1 : h->phase;
+    const long long number = h->steps + (n - left);
+    hipGraphExec_t& exec = h->graph[2 * (number & 1) + h->phase];
+    if (!exec) {
       hipGraph_t g = nullptr;
       HIP_TRY(h, hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-      for (int s = 0; s < h->graph_steps; ++s) t.step(h, s & 1);
+      (void)launch_steps(h, t, h->graph_steps, h->phase, number);
       hipError_t e = hipStreamEndCapture(h->stream, &g);
       if (e != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
         return fail(h, LBM_ERR_HIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
       }
-      e = hipGraphInstantiate(&h->graph, g, nullptr, nullptr, 0);
+      e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
       (void)hipGraphDestroy(g);
       if (e != hipSuccess) {
-        h->graph = nullptr;
+        exec = nullptr;
         return fail(h, LBM_ERR_HIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
       }
     }
-    while (h->graph && left >= h->graph_steps) {
-      HIP_TRY(h, hipGraphLaunch(h->graph, h->stream));
-      left -= h->graph_steps;
-    }
+    HIP_TRY(h, hipGraphLaunch(exec, h->stream));
+    left -= h->graph_steps;
+    h->phase = end;
   }
-  for (int s = 0; s < left; ++s) {
-    t.step(h, h->phase);
-    h->phase ^= 1;
-  }
+  h->phase = launch_steps(h, t, left, h->phase, h->steps + (n - left));
   return LBM_OK;
 }
 
@@ -1022,7 +1057,12 @@ lbm_status lbm_required_bytes(lbm_descriptor d, int nx, int ny, int nz, lbm_stor
     const PopIndex L = pop_index(qof(d), N, storage_bytes(s));
     *pop_bytes = align256(pop_elements(qof(d), L, N) * storage_bytes(s));
   }
-  if (aux_bytes) *aux_bytes = aux_layout(N, scratch_size(N)).total;
+  if (aux_bytes) {
+    const PopIndex L = pop_index(qof(d), N, storage_bytes(s));
+    const size_t pop = align256(pop_elements(qof(d), L, N) * storage_bytes(s));
+    // the second population buffer holds 32-bit byte offsets: none beyond 4 GiB
+    *aux_bytes = aux_layout(N, scratch_size(N), pop < ((size_t)1 << 32) ? pop : 0).total_with_second;
+  }
   return LBM_OK;
 }
 
@@ -1095,7 +1135,11 @@ lbm_status lbm_detail::create_lattice(lbm_lattice** out, lbm_descriptor d, int n
   h->pop_bytes = pop_bytes;
   h->aux = (unsigned char*)dev_aux;
   h->aux_bytes = aux_bytes;
-  h->lay = aux_layout(h->N, own_scratch);
+  h->lay = aux_layout(h->N, own_scratch, need_pop < ((size_t)1 << 32) ? need_pop : 0);
+  // a member of a batch is stepped by the batch
+  if (own_scratch && h->lay.total_with_second > h->lay.second &&
+      aux_bytes >= h->lay.total_with_second)
+    h->second = h->aux + h->lay.second;
   h->scratch = own_scratch ? h->aux + h->lay.scratch : shared;
   h->scratch_bytes = own_scratch ? own_scratch : shared_bytes;
   h->stream = (hipStream_t)hip_stream;
@@ -1105,6 +1149,8 @@ lbm_status lbm_detail::create_lattice(lbm_lattice** out, lbm_descriptor d, int n
   if (e == hipSuccess)
     e = hipDeviceGetAttribute(&h->lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
                               h->device);
+  if (e == hipSuccess)
+    e = hipDeviceGetAttribute(&h->num_cu, hipDeviceAttributeMultiprocessorCount, h->device);
   if (e != hipSuccess) {
     delete h;
     return fail(nullptr, LBM_ERR_HIP, std::string("device query: ") + hipGetErrorString(e));
@@ -1146,6 +1192,10 @@ lbm_status lbm_set_geometry(lbm_lattice* h, const uint8_t* material, unsigned pe
   h->nfluid = nf;
   h->has_moving_cells = hm;
   h->all_fluid = (size_t)nf == h->N;
+  h->pair = PairPlan{};
+  if (h->second)
+    h->pair = lbm_detail::make_pair_plan(h->q, h->nx, h->ny, h->nz, storage_bytes(h->storage),
+                                         !h->all_fluid, h->pix, h->num_cu);
   h->has_geometry = true;
   h->initialized = false;
   h->phase = 0;

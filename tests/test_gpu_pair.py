@@ -1,0 +1,91 @@
+"""Runs of four and more steps advance two steps per pass between two population
+buffers.  The same cell arithmetic runs in every kernel, so such a run must equal
+its steps taken one by one, and the run of a lattice created without the second
+buffer, bit for bit.  Shapes at the edges of the passes' tiles: rows of one, two
+and three waves more or less one cell, the shortest march that takes passes (4
+planes) and one that does not, one plane per work-group, odd edges, walls (some
+moving) on and off the tile borders."""
+import ctypes
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def lbm():
+    if not torch.cuda.is_available():
+        pytest.skip("no ROCm GPU visible")
+    import paper_2307_11752_amd as P
+    from paper_2307_11752_amd import _lib
+
+    _lib.load()
+    return P
+
+
+from paper_2307_11752_amd import workloads as W  # noqa: E402
+
+SHAPES = [(1, (62, 9, 4)), (1, (65, 7, 5)), (1, (64, 16, 3)), (1, (130, 6, 9)), (1, (19, 21, 40)),
+          (1, (96, 33, 12)), (1, (7, 5, 4)), (0, (254, 4, 1)), (0, (257, 37, 1)), (0, (61, 64, 1)),
+          (0, (12, 3, 1))]
+
+
+def _lattice(lbm, d, shape, storage, walls, second=True):
+    periodic = 0b001 if walls else (0b111 if d else 0b011)
+    nx, ny, nz = shape
+    mat = W.random_geometry(d, shape, periodic, seed=5) if walls else np.ones((nz, ny, nx), np.uint8)
+    lat = lbm.Lattice(d, shape, 0.7, storage=storage, shifted=storage != "f64")
+    if not second:  # recreate the handle on an aux buffer without the second population buffer
+        lib = lat.lib
+        lib.lbm_lattice_destroy(lat.h)
+        cells = nx * ny * nz
+        scratch = min(max(32 * cells, 1 << 16), 1 << 20)
+        pad = lambda b: -(-b // 256) * 256  # noqa: E731
+        aux = 2 * pad(4 * cells) + pad(cells) + 256 + pad(scratch)
+        h = ctypes.c_void_p()
+        assert lib.lbm_lattice_create(ctypes.byref(h), d, nx, ny, nz, 0.7,
+                                      {"f64": 0, "f32": 1, "f16": 2, "bf16": 3}[storage],
+                                      1 if storage != "f64" else 0,
+                                      ctypes.c_void_p(lat.pop.data_ptr()), lat.pop.numel(),
+                                      ctypes.c_void_p(lat.aux.data_ptr()), aux,
+                                      ctypes.c_void_p(lat.stream.cuda_stream)) == 0
+        lat.h = h
+    lat.set_geometry(mat, periodic)
+    lat.set_body_force((1e-4, -3e-5, 0.0))
+    lat.set_wall_velocity((0.03, 0.0, 0.0))
+    lat.init_equilibrium(W.random_density(shape, 2),
+                         W.random_velocity(shape, 3, dim=3 if d else 2))
+    return lat
+
+
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("d,shape", SHAPES)
+def test_passes_equal_single_steps(lbm, d, shape, storage, walls):
+    print(f"[pair] d={d} {shape} {storage} walls={walls}", flush=True)
+    run = _lattice(lbm, d, shape, storage, walls)
+    one = _lattice(lbm, d, shape, storage, walls)
+    alone = _lattice(lbm, d, shape, storage, walls, second=False)
+    for n in (4, 3, 9, 6):  # from both propagation phases, with every remainder
+        run.step(n)
+        alone.step(n)
+        for _ in range(n):
+            one.step(1)
+        a, b, c = run.get_populations(), one.get_populations(), alone.get_populations()
+        assert torch.equal(a, b), int((a != b).sum())
+        assert torch.equal(c, b), int((c != b).sum())
+    assert run.info()[0] == 22
+
+
+def test_too_small_aux_is_refused(lbm):
+    lat = lbm.Lattice(1, (16, 16, 16), 0.7)
+    cells, pad = 4096, 256
+    least = 9 * cells + pad + 32 * cells
+    h = ctypes.c_void_p()
+    args = (1, 16, 16, 16, 0.7, 1, 0, ctypes.c_void_p(lat.pop.data_ptr()), lat.pop.numel(),
+            ctypes.c_void_p(lat.aux.data_ptr()))
+    assert lat.lib.lbm_lattice_create(ctypes.byref(h), *args, least - 256, None) == -1
+    assert lat.lib.lbm_lattice_create(ctypes.byref(h), *args, least, None) == 0
+    assert lat.lib.lbm_lattice_destroy(h) == 0
