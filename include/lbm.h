@@ -218,7 +218,9 @@ lbm_status lbm_lattice_destroy(lbm_lattice* h);
  * sized by lbm_batch_required_bytes) and advance together: each time step
  * walks a work list of (lattice, cell range) items in one launch (one per
  * row width class in the second propagation phase), and runs of steps replay
- * as a captured HIP graph.  The update of every cell is the single-lattice
+ * as a captured HIP graph.  With FP64 and FP32 storage, where every member has
+ * at least 4 planes (D2Q9: rows), fours of steps run as two passes of two
+ * steps each; the launch shapes below apply to the remaining steps.  The update of every cell is the single-lattice
  * collide-and-stream (same cell arithmetic, same in-place AA layout).  No
  * body force, no walls.  With 16-bit storage, a member whose nx is odd keeps
  * one padding slot after every x-row in the population buffer (rows nx + 1
@@ -234,7 +236,10 @@ lbm_status lbm_lattice_destroy(lbm_lattice* h);
  * ------------------------------------------------------------------------- */
 typedef struct lbm_batch lbm_batch; /* opaque handle */
 
-/* Host-only sizes of the batch's population and aux buffers. */
+/* Host-only sizes of the batch's population and aux buffers.  The aux buffer
+ * includes the second population buffer of the two-step passes;
+ * lbm_batch_create also takes an aux buffer without it (every step then runs
+ * alone). */
 lbm_status lbm_batch_required_bytes(lbm_descriptor d, int count, const int* dims, lbm_storage s,
                                     size_t* pop_bytes, size_t* aux_bytes);
 

@@ -177,10 +177,14 @@ struct BatchLayout {
   size_t pop_total = 0, items0_off = 0, items1_off = 0, scratch_off = 0, scratch_bytes = 0,
          aux_total = 0;
   size_t max_items0 = 0, max_items1 = 0;
+  // passes of two steps: the work list and the second population buffer follow the rest
+  PairBatchPlan pair;
+  size_t pair_items_off = 0, second_off = 0, total_with_second = 0;
 };
 
-lbm_status batch_layout(lbm_descriptor d, int count, const int* dims, lbm_storage s,
-                        BatchLayout* L, std::string* why) {
+// tau: NULL where only the sizes matter
+lbm_status batch_layout(lbm_descriptor d, int count, const int* dims, const double* tau,
+                        lbm_storage s, BatchLayout* L, std::string* why) {
   if (count <= 0 || !dims) {
     *why = "count must be positive and dims non-NULL";
     return LBM_ERR_ARG;
@@ -227,7 +231,22 @@ lbm_status batch_layout(lbm_descriptor d, int count, const int* dims, lbm_storag
   L->max_items1 = items1;
   L->scratch_off = align256(L->items1_off + sizeof(BatchItem) * items1);
   L->scratch_bytes = scratch_size(max_cells);
-  L->aux_total = align256(L->scratch_off + L->scratch_bytes);
+  L->aux_total = L->total_with_second = align256(L->scratch_off + L->scratch_bytes);
+  {
+    std::vector<PairMember> members;
+    for (int b = 0; b < count; ++b) {
+      const int nx = dims[3 * b], ny = dims[3 * b + 1], nz = dims[3 * b + 2];
+      const int px = member_pitch(nx, storage_bytes(s));
+      members.push_back({nx, ny, nz, px, pop_index(qof(d), (size_t)px * ny * nz, storage_bytes(s)),
+                         L->pop_off[b] / storage_bytes(s), tau && !std::isinf(tau[b]) ? 1.0 / tau[b] : 0.0});
+    }
+    L->pair = lbm_detail::make_pair_batch_plan(qof(d), storage_bytes(s), members, 256 /* compute units */);
+    if (!L->pair.items.empty()) {
+      L->pair_items_off = L->aux_total;
+      L->second_off = align256(L->pair_items_off + sizeof(PairItem) * L->pair.items.size());
+      L->total_with_second = L->second_off + pop;
+    }
+  }
   return LBM_OK;
 }
 
@@ -256,8 +275,12 @@ struct lbm_batch {
   // the device item tables match nitems0 / nitems1 / lane_*; false after a
   // HIP failure while uploading them (stepping is refused until a rebuild)
   bool tables_ok = false;
+  // Passes of two steps, from `pop` to `second` and back, an even number of
+  // them at a time (null: no room, or they do not apply)
+  void* second = nullptr;
+  // replays of graph_steps steps, per propagation phase they start in
   int graph_steps = 0;
-  hipGraphExec_t graph = nullptr;
+  hipGraphExec_t graph[2] = {nullptr, nullptr};
   std::string err;
 };
 
@@ -276,11 +299,12 @@ lbm_status bfail(lbm_batch* b, lbm_status st, const std::string& msg) {
   } while (0)
 
 void drop_batch_graph(lbm_batch* b) {
-  if (b->graph) {
-    // a replay may still be running on the batch's stream
-    (void)hipStreamSynchronize(b->stream);
-    (void)hipGraphExecDestroy(b->graph);
-    b->graph = nullptr;
+  if (!b->graph[0] && !b->graph[1]) return;
+  // a replay may still be running on the batch's stream
+  (void)hipStreamSynchronize(b->stream);
+  for (hipGraphExec_t& g : b->graph) {
+    if (g) (void)hipGraphExecDestroy(g);
+    g = nullptr;
   }
 }
 
@@ -398,48 +422,75 @@ lbm_status common_phase(lbm_batch* b, int* phase) {
   return LBM_OK;
 }
 
-void advance_views(lbm_batch* b, int n) {
+void advance_views(lbm_batch* b, int n, int phase) {
   for (lbm_lattice* v : b->views) {
-    v->phase ^= (n & 1);
+    v->phase = phase;
     v->steps += n;
   }
 }
 
-// Enqueue n steps of every member from propagation phase `phase` (graph
-// replays where set up).  Returns LBM_ERR_HIP on a HIP failure.
-lbm_status enqueue_batch_steps(lbm_batch* b, int n, int phase) {
-  int left = n;
-  if (b->graph_steps > 0 && n >= b->graph_steps) {
-    if (phase != 0) {
-      launch_one(b, 1);
-      phase = 0;
-      --left;
+void launch_pair(lbm_batch* b, bool to_second, bool entry) {
+  PairBatchLaunch a{};
+  a.items = (const PairItem*)(b->aux + b->lay.pair_items_off);
+  a.nitems = (int)b->lay.pair.items.size();
+  a.threads = b->lay.pair.threads;
+  a.small = b->lay.pair.small;
+  a.src = to_second ? b->pop : b->second;
+  a.dst = to_second ? b->second : b->pop;
+  a.entry = entry;
+  a.stream = b->stream;
+  // (the plan is empty for 16-bit storage)
+  b->storage == LBM_STORE_F64 ? lbm_detail::launch_pair_batch<double>(b->q, b->shifted, a)
+                              : lbm_detail::launch_pair_batch<float>(b->q, b->shifted, a);
+}
+
+// Launch n steps from propagation phase `phase`; returns the phase they end
+// in.  Fours of steps run as two passes, there and back (leaving phase 1).
+int launch_steps(lbm_batch* b, int n, int phase) {
+  if (b->second) {
+    for (; n >= 4; n -= 4) {
+      launch_pair(b, true, phase == 0);
+      launch_pair(b, false, false);
+      phase = 1;
     }
-    if (!b->graph && left >= b->graph_steps) {
+  }
+  for (; n > 0; --n) {
+    launch_one(b, phase);
+    phase ^= 1;
+  }
+  return phase;
+}
+
+// Enqueue n steps of every member from propagation phase *phase (graph
+// replays where set up), which is left as the one they end in.  Returns
+// LBM_ERR_HIP on a HIP failure.
+lbm_status enqueue_batch_steps(lbm_batch* b, int n, int* phase) {
+  int left = n;
+  while (b->graph_steps > 0 && left >= b->graph_steps) {
+    hipGraphExec_t& exec = b->graph[*phase];
+    int end = *phase;
+    if (b->second && b->graph_steps >= 4) end = 1;  // an even run after passes
+    if (!exec) {
       hipGraph_t g = nullptr;
       BHIP_TRY(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-      for (int s = 0; s < b->graph_steps; ++s) launch_one(b, s & 1);
+      (void)launch_steps(b, b->graph_steps, *phase);
       hipError_t e = hipStreamEndCapture(b->stream, &g);
       if (e != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
         return bfail(b, LBM_ERR_HIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
       }
-      e = hipGraphInstantiate(&b->graph, g, nullptr, nullptr, 0);
+      e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
       (void)hipGraphDestroy(g);
       if (e != hipSuccess) {
-        b->graph = nullptr;
+        exec = nullptr;
         return bfail(b, LBM_ERR_HIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
       }
     }
-    while (b->graph && left >= b->graph_steps) {
-      BHIP_TRY(b, hipGraphLaunch(b->graph, b->stream));
-      left -= b->graph_steps;
-    }
+    BHIP_TRY(b, hipGraphLaunch(exec, b->stream));
+    left -= b->graph_steps;
+    *phase = end;
   }
-  for (int s = 0; s < left; ++s) {
-    launch_one(b, phase);
-    phase ^= 1;
-  }
+  *phase = launch_steps(b, left, *phase);
   return LBM_OK;
 }
 
@@ -451,10 +502,10 @@ lbm_status lbm_batch_required_bytes(lbm_descriptor d, int count, const int* dims
                                     size_t* pop_bytes, size_t* aux_bytes) {
   BatchLayout L;
   std::string why;
-  lbm_status st = batch_layout(d, count, dims, s, &L, &why);
+  lbm_status st = batch_layout(d, count, dims, nullptr, s, &L, &why);
   if (st) return lbm_detail::fail(nullptr, st, why);
   if (pop_bytes) *pop_bytes = L.pop_total;
-  if (aux_bytes) *aux_bytes = L.aux_total;
+  if (aux_bytes) *aux_bytes = L.total_with_second;
   return LBM_OK;
 }
 
@@ -465,7 +516,7 @@ lbm_status lbm_batch_create(lbm_batch** out, lbm_descriptor d, int count, const 
   *out = nullptr;
   BatchLayout L;
   std::string why;
-  lbm_status st = batch_layout(d, count, dims, s, &L, &why);
+  lbm_status st = batch_layout(d, count, dims, tau, s, &L, &why);
   if (st) return lbm_detail::fail(nullptr, st, why);
   if (!tau) return lbm_detail::fail(nullptr, LBM_ERR_ARG, "tau is NULL");
   if (!dev_pop || !dev_aux) return lbm_detail::fail(nullptr, LBM_ERR_ARG, "device buffers must not be NULL");
@@ -484,6 +535,7 @@ lbm_status lbm_batch_create(lbm_batch** out, lbm_descriptor d, int count, const 
   b->aux = (unsigned char*)dev_aux;
   b->stream = (hipStream_t)hip_stream;
   b->lay = L;
+  if (!L.pair.items.empty() && aux_bytes >= L.total_with_second) b->second = b->aux + L.second_off;
   auto undo = [&](lbm_status code, const std::string& msg) {
     for (lbm_lattice* v : b->views) {
       v->batch = nullptr;
@@ -531,6 +583,13 @@ lbm_status lbm_batch_create(lbm_batch** out, lbm_descriptor d, int count, const 
     b->max_tpr = std::max(b->max_tpr, bl.tpr);
     b->lats.push_back(bl);
     b->total_cells += (long long)v->N;
+  }
+  if (b->second) {
+    const std::vector<PairItem>& items = b->lay.pair.items;
+    if (hipMemcpyAsync(b->aux + L.pair_items_off, items.data(), sizeof(PairItem) * items.size(),
+                       hipMemcpyHostToDevice, b->stream) != hipSuccess ||
+        hipStreamSynchronize(b->stream) != hipSuccess)
+      return undo(LBM_ERR_HIP, "upload of the work list failed");
   }
   int t0 = 128;
   while (t0 < b->max_tpr) t0 *= 2;
@@ -612,7 +671,7 @@ lbm_status lbm_batch_step(lbm_batch* b, int n) {
   int phase = 0;
   st = common_phase(b, &phase);
   if (st) return st;
-  st = enqueue_batch_steps(b, n, phase);
+  st = enqueue_batch_steps(b, n, &phase);
   if (st == LBM_OK) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
@@ -625,7 +684,7 @@ lbm_status lbm_batch_step(lbm_batch* b, int n) {
     drop_batch_graph(b);
     return st;
   }
-  advance_views(b, n);
+  advance_views(b, n, phase);
   return LBM_OK;
 }
 
@@ -665,7 +724,7 @@ lbm_status time_trial(lbm_batch* b, int phase, int trial_steps, std::vector<hipE
   ms[0] /= trial_steps / 2;
   ms[1] /= trial_steps / 2;
   *total = 0.5 * (ms[0] + ms[1]);
-  advance_views(b, trial_steps + 2);
+  advance_views(b, trial_steps + 2, phase);
   return LBM_OK;
 }
 

@@ -42,6 +42,37 @@ __global__ void __launch_bounds__((pair_columns<Q, S, SMALL>()))
                                              z0, min(z0 + G.ZC, G.nz), p);
 }
 
+#if LBM_PAIR_STORAGE <= 1
+// The same pass over a batch: one work-group per item of the work list.  Members
+// differ in the columns of a tile, so waves past an item's last column end at
+// once (a barrier waits for the surviving waves only).
+template <int Q, typename S, bool SHIFT, bool SMALL>
+__global__ void __launch_bounds__((pair_columns<Q, S, SMALL>()))
+    pair_batch_kernel(const S* __restrict__ src, S* __restrict__ dst,
+                      const PairItem* __restrict__ items, int entry) {
+  const PairItem& it = items[blockIdx.x];
+  if (it.z0 == it.z1) return;
+  const PairGeom G = it.geom;
+  if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) * 64 >= G.W * G.H) return;
+  StepParams<typename Store<S>::T> p{};
+  p.base = (typename Store<S>::T)Store<S>::unit;
+  p.omega = (typename Store<S>::T)it.omega;
+  pair_pass<Q, S, SHIFT, false, false, SMALL>(src + it.pop_off, dst + it.pop_off, nullptr, nullptr,
+                                              G, entry != 0, it.tile, it.z0, it.z1, p);
+}
+
+template <int Q, bool SHIFT>
+void launch_batch(const PairBatchLaunch& a) {
+  const dim3 grid((unsigned)a.nitems), block((unsigned)a.threads);
+  if (a.small)
+    hipLaunchKernelGGL((pair_batch_kernel<Q, Stored, SHIFT, true>), grid, block, 0, a.stream,
+                       (const Stored*)a.src, (Stored*)a.dst, a.items, a.entry);
+  else
+    hipLaunchKernelGGL((pair_batch_kernel<Q, Stored, SHIFT, false>), grid, block, 0, a.stream,
+                       (const Stored*)a.src, (Stored*)a.dst, a.items, a.entry);
+}
+#endif
+
 template <int Q, bool SHIFT, bool MASKED>
 void launch(const PairLaunch& a, const StepParams<typename Store<Stored>::T>& p) {
   const PairGeom& G = a.plan->geom;
@@ -76,3 +107,13 @@ void lbm_detail::launch_pair<Stored>(int q, bool shifted, bool masked, const Pai
       masked ? launch<19, false, true>(a, p) : launch<19, false, false>(a, p);
   }
 }
+
+#if LBM_PAIR_STORAGE <= 1
+template <>
+void lbm_detail::launch_pair_batch<Stored>(int q, bool shifted, const PairBatchLaunch& a) {
+  if (q == 9)
+    shifted ? launch_batch<9, true>(a) : launch_batch<9, false>(a);
+  else
+    shifted ? launch_batch<19, true>(a) : launch_batch<19, false>(a);
+}
+#endif

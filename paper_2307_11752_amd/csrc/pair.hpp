@@ -6,6 +6,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 #include "lattice.hpp"
 
@@ -14,8 +15,10 @@
 //   separable placements (whole planes per chunk, or one array per population):
 //     i pb + z zb + s r + ((s r) >> sh) kb;
 //   else, with c = s (r + z nx ny):  i pb + c + (c >> sh) kb  (PopIndex in bytes).
+// (px instead of nx where rows are padded).
 struct PairGeom {
   int nx, ny, nz;
+  int px;               // cells from one stored row to the next
   int TX, TY, W, H;     // columns of a tile without and with its halo
   int ntx, tiles, ZC;   // tiles per row of tiles and per plane, planes per block
   int nblocks;
@@ -42,6 +45,40 @@ struct PairLaunch {
   hipStream_t stream;
 };
 
+// One work-group of a batch's pass: planes z0 .. z1 - 1 of a tile of a member
+// (z0 == z1: nothing).
+struct PairItem {
+  PairGeom geom;
+  int tile, z0, z1;
+  uint64_t pop_off;  // elements from the start of the batch's populations
+  double omega;
+};
+
+struct PairBatchLaunch {
+  const PairItem* items;
+  int nitems, threads;
+  bool small;
+  const void* src;
+  void* dst;
+  int entry;
+  hipStream_t stream;
+};
+
+// What the plan of a batch needs to know of a member.
+struct PairMember {
+  int nx, ny, nz, px;
+  lbm::PopIndex pix;
+  uint64_t pop_off;
+  double omega;
+};
+
+// The work list of a batch's pass, in launch order; empty: it does not pay or apply.
+struct PairBatchPlan {
+  std::vector<PairItem> items;
+  bool small = false;
+  int threads = 0;
+};
+
 // Columns (threads) of a work-group at most: two planes of populations fit one
 // CU's LDS (160 KB), or, small, several work-groups to a CU.
 constexpr int pair_column_limit(int q, size_t s, bool small) {
@@ -54,6 +91,12 @@ namespace lbm_detail {
 // 2^32 bytes or more) or does not pay.
 PairPlan make_pair_plan(int q, int nx, int ny, int nz, size_t s, bool masked,
                         const lbm::PopIndex& L, int num_cu);
+
+PairBatchPlan make_pair_batch_plan(int q, size_t s, const std::vector<PairMember>& members,
+                                   int num_cu);
+
+template <typename S>
+void launch_pair_batch(int q, bool shifted, const PairBatchLaunch& a);
 
 template <typename S>
 void launch_pair(int q, bool shifted, bool masked, const PairLaunch& a,

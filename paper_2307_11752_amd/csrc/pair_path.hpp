@@ -147,13 +147,13 @@ __device__ __forceinline__ void pair_pass(const S* __restrict__ src, S* __restri
     for (int a = 0; a < 3; ++a)
 #pragma unroll
       for (int b = 0; b < (D3 ? 3 : 1); ++b) {
-        const uint32_t c = SB * ((uint32_t)G.nx * (uint32_t)Y[D3 ? b : 1] + (uint32_t)X[a]);
+        const uint32_t c = SB * ((uint32_t)G.px * (uint32_t)Y[D3 ? b : 1] + (uint32_t)X[a]);
         nb[a][b] = SEP ? c + __umul24(c >> G.sh, G.kb) : c;
       }
-    r1 = (uint32_t)G.nx * (uint32_t)y + (uint32_t)x;
+    r1 = (uint32_t)G.px * (uint32_t)y + (uint32_t)x;
   }
   constexpr int MID = D3 ? 1 : 0;
-  const uint32_t np = (uint32_t)G.nx * (uint32_t)G.ny;
+  const uint32_t np = (uint32_t)G.px * (uint32_t)G.ny;
   const __amdgpu_buffer_rsrc_t rs =
       __builtin_amdgcn_make_buffer_rsrc((void*)src, 0, G.bytes, 0x00027000);
   // lane and scalar part of the address of in-plane offset o in plane z (slot 0)
@@ -277,7 +277,7 @@ __device__ __forceinline__ void pair_pass(const S* __restrict__ src, S* __restri
     cx2 = min(cx2, G.nx - 1 - txi * G.TX);
     if (D3) cy2 = min(cy2, G.ny - 1 - tyi * G.TY);
   }
-  const uint32_t r2 = (uint32_t)G.nx * (uint32_t)(D3 ? tyi * G.TY + cy2 : 0) + (uint32_t)(txi * G.TX + cx2);
+  const uint32_t r2 = (uint32_t)G.px * (uint32_t)(D3 ? tyi * G.TY + cy2 : 0) + (uint32_t)(txi * G.TX + cx2);
   const uint32_t out0 = SEP ? r2 * SB + __umul24((r2 * SB) >> G.sh, G.kb) : r2 * SB;
   const int c2 = (D3 ? (cy2 + 1) * G.W : 0) + cx2 + 1;
   const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(dst, 0, G.bytes, 0x00027000);

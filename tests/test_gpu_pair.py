@@ -89,3 +89,35 @@ def test_too_small_aux_is_refused(lbm):
     assert lat.lib.lbm_lattice_create(ctypes.byref(h), *args, least - 256, None) == -1
     assert lat.lib.lbm_lattice_create(ctypes.byref(h), *args, least, None) == 0
     assert lat.lib.lbm_lattice_destroy(h) == 0
+
+
+BATCHES = {
+    "boxes": (1, [(62, 9, 4), (65, 7, 5), (16, 16, 16), (33, 21, 40), (7, 5, 4), (130, 6, 9)]),
+    "cut": (1, [(48, 40, 44)] * 3 + [(9, 8, 11)] * 17),  # members cut over the XCDs and whole ones
+    "planes": (0, [(254, 4, 1), (257, 37, 1), (61, 64, 1), (12, 5, 1)]),
+    "short": (1, [(20, 12, 10), (9, 9, 3)]),  # a march too short: the batch steps in place
+}
+
+
+@pytest.mark.parametrize("graph", [0, 6])
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("name", BATCHES)
+def test_batch_passes_equal_single_steps(lbm, name, storage, graph):
+    print(f"[pair] batch {name} {storage} graph={graph}", flush=True)
+    d, shapes = BATCHES[name]
+    taus = [0.55 + 0.4 * k / len(shapes) for k in range(len(shapes))]
+    runs = [lbm.Batch(d, shapes, taus, storage=storage, shifted=storage != "f64") for _ in range(2)]
+    runs[0].set_graph_steps(graph)
+    for b in runs:
+        for k, (m, s) in enumerate(zip(b, shapes)):
+            m.init_equilibrium(W.random_density(s, k), W.random_velocity(s, k, dim=3 if d else 2))
+    for n in (4, 3, 9, 6, 13):
+        runs[0].step(n)
+        for _ in range(n):
+            runs[1].step(1)
+        for a, b in zip(*runs):
+            x, y = a.get_populations(), b.get_populations()
+            assert torch.equal(x, y), (a.index, int((x != y).sum()))
+    assert runs[0][0].info()[0] == 35
+    for b in runs:
+        b.close()
