@@ -31,7 +31,8 @@ _CSRC = os.path.join("paper_2307_11752_amd", "csrc")
 KERNEL_SOURCES = {
     "lattice": [os.path.join(_CSRC, n) for n in ("lbm.hip", "lattice.hpp", "fluid_path.hpp",
                                                   "handle.hpp", "pair.hip", "pair.hpp",
-                                                  "pair_path.hpp", "pair_plan.hip")] + ["include/lbm.h"],
+                                                  "pair_path.hpp", "pair_plan.hip", "deep.hip",
+                                                  "deep.hpp", "deep_plan.hip")] + ["include/lbm.h"],
     "batch": [os.path.join(_CSRC, n) for n in ("batch.hip", "lattice.hpp", "fluid_path.hpp",
                                                 "handle.hpp")] + ["include/lbm.h"],
     "porous": [os.path.join(_CSRC, n) for n in ("adjoint.hip", "lattice.hpp", "handle.hpp")]

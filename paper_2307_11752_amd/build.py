@@ -10,10 +10,10 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
-# (object name, source, extra flags): pair.hip is compiled once per storage type
-UNITS = [(n, os.path.join(CSRC, n + ".hip"), ()) for n in ("lbm", "batch", "adjoint", "pair_plan")] \
-    + [(f"pair_{t}", os.path.join(CSRC, "pair.hip"), (f"-DLBM_PAIR_STORAGE={k}",))
-       for k, t in enumerate(("f64", "f32", "f16", "bf16"))]
+# (object name, source, extra flags): pair.hip and deep.hip are compiled once per storage type
+UNITS = [(n, os.path.join(CSRC, n + ".hip"), ()) for n in ("lbm", "batch", "adjoint", "pair_plan", "deep_plan")] \
+    + [(f"{n}_{t}", os.path.join(CSRC, n + ".hip"), (f"-DLBM_PAIR_STORAGE={k}",))
+       for n in ("pair", "deep") for k, t in enumerate(("f64", "f32", "f16", "bf16"))]
 LIB = os.path.join(HERE, "liblbm_hip.so")
 ARCH = "gfx950"
 

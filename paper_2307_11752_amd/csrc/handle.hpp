@@ -11,6 +11,7 @@
 
 #include "lattice.hpp"
 #include "lbm.h"
+#include "deep.hpp"
 #include "pair.hpp"
 
 constexpr int RED_BLOCKS = 1024;
@@ -134,6 +135,7 @@ struct lbm_lattice {
   // `pop` between calls.  Null second: the aux buffer has no room for it.
   void* second = nullptr;
   PairPlan pair{};
+  DeepPlan deep{};  // D2Q9: many steps per pass (deep.hip), in the same way
   // Replay of captured runs of graph_steps steps (0 = direct launches), one
   // per propagation phase they start in and parity of their first step.  The
   // graphs bake in the kernel arguments, so any parameter change drops them.

@@ -811,12 +811,22 @@ struct Ops {
   }
 
   // Two steps from src (natural form: entry) to dst.
+  static void deep(lbm_lattice* h, const void* src, void* dst, int steps, bool entry,
+                   long long number) {
+    StepParams<T> p = make_params<T>(h, number);
+    p.base = (T)Store<S>::unit;
+    const DeepLaunch a{&h->deep, h->nx, h->ny, h->pix, steps, src, dst,
+                       (const uint32_t*)(h->aux + h->lay.link),
+                       (const uint32_t*)(h->aux + h->lay.mov), entry ? 1 : 0, h->stream};
+    lbm_detail::launch_deep<S>(SHIFT, !h->all_fluid, a, p);
+  }
+
   static void pair(lbm_lattice* h, const void* src, void* dst, bool entry, long long number) {
     StepParams<T> p = make_params<T>(h, number);
     p.base = (T)Store<S>::unit;
     const PairLaunch a{&h->pair, src, dst, (const uint32_t*)(h->aux + h->lay.link),
                        (const uint32_t*)(h->aux + h->lay.mov), entry ? 1 : 0, h->stream};
-    lbm_detail::launch_pair<S>(Q, SHIFT, !h->all_fluid, a, p);
+    lbm_detail::launch_pair<S>(SHIFT, !h->all_fluid, a, p);
   }
 
   static unsigned blocks(size_t N) {
@@ -867,6 +877,7 @@ struct Ops {
 struct OpTable {
   void (*step)(lbm_lattice*, int, long long);
   void (*pair)(lbm_lattice*, const void*, void*, bool, long long);
+  void (*deep)(lbm_lattice*, const void*, void*, int, bool, long long);
   void (*get_pop)(lbm_lattice*, double*);
   void (*set_pop)(lbm_lattice*, const double*);
   void (*init_eq)(lbm_lattice*, const double*, const double*);
@@ -878,7 +889,7 @@ struct OpTable {
 template <int Q, typename S, bool SHIFT>
 OpTable table() {
   using O = Ops<Q, S, SHIFT>;
-  return OpTable{O::step, O::pair, O::get_pop, O::set_pop, O::init_eq, O::moments_f64, O::moments_f32,
+  return OpTable{O::step, O::pair, O::deep, O::get_pop, O::set_pop, O::init_eq, O::moments_f64, O::moments_f32,
                  O::totals};
 }
 
@@ -985,10 +996,23 @@ lbm_status reduce_totals(lbm_lattice* h, double* partials, double* result, doubl
 }
 
 // Launch n steps from propagation phase `phase`, the first of them number
-// `number` since the initialisation; returns the phase they end in.  Whole
-// fours of steps run as two passes of two steps, there and back between the
-// two population buffers (leaving phase 1), the others one by one in place.
+// `number` since the initialisation; returns the phase they end in.  Where the
+// lattice takes passes, they go there and back between the two population
+// buffers and leave phase 1: D2Q9 an even number of about equal ones from four
+// steps on, D3Q19 two of two steps for every four.  Other steps run one by one
+// in place.
 int launch_steps(lbm_lattice* h, const OpTable& t, int n, int phase, long long number) {
+  if (h->deep.use && h->second && n >= 4) {
+    for (int left = (n + 2 * h->deep.steps - 1) / (2 * h->deep.steps) * 2; left > 0; --left) {
+      const int k = (n + left - 1) / left;
+      t.deep(h, left % 2 == 0 ? h->pop : h->second, left % 2 == 0 ? h->second : h->pop, k, phase == 0,
+             number);
+      n -= k;
+      number += k;
+      phase = 1;
+    }
+    return phase;
+  }
   if (h->pair.use && h->second) {
     for (; n >= 4; n -= 4, number += 4) {
       t.pair(h, h->pop, h->second, phase == 0, number);
@@ -1011,7 +1035,7 @@ lbm_status enqueue_steps(lbm_lattice* h, int n) {
   while (h->graph_steps > 0 && left >= h->graph_steps) {
     // the phase a run of this length ends in (its length is even: the phase it
     // starts in, unless it takes passes of two steps)
-    const bool pairs = h->pair.use && h->second && h->graph_steps >= 4;
+    const bool pairs = (h->pair.use || h->deep.use) && h->second && h->graph_steps >= 4;
     const int end = pairs ? 1 : h->phase;
     const long long number = h->steps + (n - left);
     hipGraphExec_t& exec = h->graph[2 * (number & 1) + h->phase];
@@ -1193,8 +1217,11 @@ lbm_status lbm_set_geometry(lbm_lattice* h, const uint8_t* material, unsigned pe
   h->has_moving_cells = hm;
   h->all_fluid = (size_t)nf == h->N;
   h->pair = PairPlan{};
-  if (h->second)
-    h->pair = lbm_detail::make_pair_plan(h->q, h->nx, h->ny, h->nz, storage_bytes(h->storage),
+  h->deep = DeepPlan{};
+  if (h->second && h->q == 9)
+    h->deep = lbm_detail::make_deep_plan(h->nx, h->ny, storage_bytes(h->storage), h->num_cu);
+  else if (h->second)
+    h->pair = lbm_detail::make_pair_plan(h->nx, h->ny, h->nz, storage_bytes(h->storage),
                                          !h->all_fluid, h->pix, h->num_cu);
   h->has_geometry = true;
   h->initialized = false;

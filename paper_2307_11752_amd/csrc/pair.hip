@@ -73,39 +73,32 @@ void launch_batch(const PairBatchLaunch& a) {
 }
 #endif
 
-template <int Q, bool SHIFT, bool MASKED>
+template <bool SHIFT, bool MASKED>
 void launch(const PairLaunch& a, const StepParams<typename Store<Stored>::T>& p) {
   const PairGeom& G = a.plan->geom;
   const dim3 grid((unsigned)((G.nblocks + 7) / 8 * 8)), block((unsigned)((G.W * G.H + 63) / 64 * 64));
   const Stored* src = (const Stored*)a.src;
   Stored* dst = (Stored*)a.dst;
   if (a.plan->small)
-    hipLaunchKernelGGL((pair_kernel<Q, Stored, SHIFT, MASKED, false, true>), grid, block, 0,
+    hipLaunchKernelGGL((pair_kernel<19, Stored, SHIFT, MASKED, false, true>), grid, block, 0,
                        a.stream, src, dst, a.link, a.mov, G, a.entry, p);
-  else if (Q == 19 && MASKED && a.plan->separable)
-    hipLaunchKernelGGL((pair_kernel<Q, Stored, SHIFT, MASKED, Q == 19 && MASKED, false>), grid, block, 0,
+  else if (MASKED && a.plan->separable)
+    hipLaunchKernelGGL((pair_kernel<19, Stored, SHIFT, MASKED, MASKED, false>), grid, block, 0,
                        a.stream, src, dst, a.link, a.mov, G, a.entry, p);
   else
-    hipLaunchKernelGGL((pair_kernel<Q, Stored, SHIFT, MASKED, false, false>), grid, block, 0,
+    hipLaunchKernelGGL((pair_kernel<19, Stored, SHIFT, MASKED, false, false>), grid, block, 0,
                        a.stream, src, dst, a.link, a.mov, G, a.entry, p);
 }
 
 }  // namespace
 
 template <>
-void lbm_detail::launch_pair<Stored>(int q, bool shifted, bool masked, const PairLaunch& a,
+void lbm_detail::launch_pair<Stored>(bool shifted, bool masked, const PairLaunch& a,
                                      const StepParams<typename Store<Stored>::T>& p) {
-  if (q == 9) {
-    if (shifted)
-      masked ? launch<9, true, true>(a, p) : launch<9, true, false>(a, p);
-    else
-      masked ? launch<9, false, true>(a, p) : launch<9, false, false>(a, p);
-  } else {
-    if (shifted)
-      masked ? launch<19, true, true>(a, p) : launch<19, true, false>(a, p);
-    else
-      masked ? launch<19, false, true>(a, p) : launch<19, false, false>(a, p);
-  }
+  if (shifted)
+    masked ? launch<true, true>(a, p) : launch<true, false>(a, p);
+  else
+    masked ? launch<false, true>(a, p) : launch<false, false>(a, p);
 }
 
 #if LBM_PAIR_STORAGE <= 1

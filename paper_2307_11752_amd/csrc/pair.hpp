@@ -86,10 +86,10 @@ constexpr int pair_column_limit(int q, size_t s, bool small) {
 }
 
 namespace lbm_detail {
-// Tiles for a lattice of nx x ny x nz cells (host only; num_cu compute units).
+// Tiles for a D3Q19 lattice of nx x ny x nz cells (host only; num_cu compute units).
 // plan.use is false where the pass does not apply (a population buffer of
 // 2^32 bytes or more) or does not pay.
-PairPlan make_pair_plan(int q, int nx, int ny, int nz, size_t s, bool masked,
+PairPlan make_pair_plan(int nx, int ny, int nz, size_t s, bool masked,
                         const lbm::PopIndex& L, int num_cu);
 
 PairBatchPlan make_pair_batch_plan(int q, size_t s, const std::vector<PairMember>& members,
@@ -99,6 +99,6 @@ template <typename S>
 void launch_pair_batch(int q, bool shifted, const PairBatchLaunch& a);
 
 template <typename S>
-void launch_pair(int q, bool shifted, bool masked, const PairLaunch& a,
+void launch_pair(bool shifted, bool masked, const PairLaunch& a,
                  const lbm::StepParams<typename lbm::Store<S>::T>& p);
 }  // namespace lbm_detail

@@ -101,8 +101,9 @@ void set_tiles(PairGeom& g, int q, int TX, int TY, int ntx, int nty, int ZC) {
 
 }  // namespace
 
-PairPlan lbm_detail::make_pair_plan(int q, int nx, int ny, int nz, size_t s, bool masked,
+PairPlan lbm_detail::make_pair_plan(int nx, int ny, int nz, size_t s, bool masked,
                                     const lbm::PopIndex& L, int num_cu) {
+  constexpr int q = 19;
   PairPlan best;
   PairGeom g{};
   if (!set_geometry(g, &best.separable, q, nx, ny, nz, nx, s, L)) return best;
@@ -112,7 +113,7 @@ PairPlan lbm_detail::make_pair_plan(int q, int nx, int ny, int nz, size_t s, boo
   const Model m{q, s, masked, is_big((double)N, q, s)};
   for (bool small : {false, true})
     each_tile(g, q, pair_column_limit(q, s, small), [&](int TX, int TY, int ntx, int nty) {
-      const int W = TX + 2, H = q == 9 ? 1 : TY + 2, per_cu = m.per_cu(W * H, small);
+      const int W = TX + 2, H = TY + 2, per_cu = m.per_cu(W * H, small);
       for (int nzc = 1; nzc <= g.nz; ++nzc) {
         const int ZC = ceil_div(g.nz, nzc);
         if (ceil_div(g.nz, ZC) != nzc) continue;
@@ -141,7 +142,7 @@ PairPlan lbm_detail::make_pair_plan(int q, int nx, int ny, int nz, size_t s, boo
   // / 23.1) and larger ones lose (192^3 103 / 124).
   const bool wave_rows = nx % 4 == 0 && nx <= 256 && ((nx / 4) & (nx / 4 - 1)) == 0;
   const bool some = best.cost < 1e300;
-  if (s != 2 || q == 9)
+  if (s != 2)
     best.use = some;
   else if (masked)
     best.use = some && N <= 1100000;

@@ -121,3 +121,25 @@ def test_batch_passes_equal_single_steps(lbm, name, storage, graph):
     assert runs[0][0].info()[0] == 35
     for b in runs:
         b.close()
+
+
+# Regions of 256 to 4096 cells, narrower and wider than the lattice, passes of
+# different lengths in one run; the walled 512 x 300 takes the flat in-place kernel.
+DEEP_SHAPES = [(5, 4, 1), (17, 9, 1), (64, 64, 1), (130, 51, 1), (333, 201, 1), (512, 300, 1),
+               (1023, 511, 1)]
+
+
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("shape", DEEP_SHAPES)
+def test_deep_passes_equal_single_steps(lbm, shape, storage, walls):
+    print(f"[deep] {shape} {storage} walls={walls}", flush=True)
+    run = _lattice(lbm, 0, shape, storage, walls)
+    one = _lattice(lbm, 0, shape, storage, walls)
+    for n in (4, 1, 31, 5, 18):
+        run.step(n)
+        for _ in range(n):
+            one.step(1)
+        a, b = run.get_populations(), one.get_populations()
+        assert torch.equal(a, b), int((a != b).sum())
+    assert run.info()[0] == 59
