@@ -23,6 +23,7 @@
 // index; fluid cells never touch a non-periodic edge (geometry check).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -1342,11 +1343,18 @@ lbm_status lbm_moments(lbm_lattice* h, double* rho, double* u) {
   st = readable(h);
   if (st) return st;
   if (!rho && !u) return LBM_OK;
-  // cells are decoded in chunks into the scratch (rho, then the three u
-  // components, each `chunk` doubles) and copied out; the host waits for each
+  // Cells are decoded in chunks (rho, then the three u components, each `chunk`
+  // doubles) and copied out; the host waits for each.  The second population
+  // buffer, free between calls, takes them all at once (D2Q9 in 16 bits half of
+  // them): two copies instead of four for every 32768 cells of the scratch
+  // (128 x 96 x 80: 2.82 ms a call through the scratch).
   const OpTable t = ops(h);
-  const size_t chunk = h->scratch_bytes / MOMENT_BYTES_PER_CELL;
-  double* sr = (double*)h->scratch;
+  const size_t room = h->second ? pop_elements(h->q, h->pix, (size_t)h->px * h->ny * h->nz) *
+                                      storage_bytes(h->storage) / MOMENT_BYTES_PER_CELL
+                                : 0;
+  const bool wide = room * MOMENT_BYTES_PER_CELL > h->scratch_bytes;
+  const size_t chunk = std::min(wide ? room : h->scratch_bytes / MOMENT_BYTES_PER_CELL, h->N);
+  double* sr = (double*)(wide ? h->second : h->scratch);
   double* su = sr + chunk;
   for (size_t begin = 0; begin < h->N; begin += chunk) {
     const size_t n = h->N - begin < chunk ? h->N - begin : chunk;
@@ -1357,7 +1365,9 @@ lbm_status lbm_moments(lbm_lattice* h, double* rho, double* u) {
     if (rho)
       HIP_TRY(h, hipMemcpyAsync(rho + begin, sr, n * sizeof(double), hipMemcpyDeviceToHost,
                                 h->stream));
-    if (u)
+    if (u && n == h->N)
+      HIP_TRY(h, hipMemcpyAsync(u, su, 3 * n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    else if (u)
       for (int a = 0; a < 3; ++a)
         HIP_TRY(h, hipMemcpyAsync(u + (size_t)a * h->N + begin, su + (size_t)a * chunk,
                                   n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
