@@ -296,40 +296,61 @@ __global__ void fill_kernel(float* __restrict__ a, size_t n, float v) {
     a[k] = v;
 }
 
-// Objective (one block): mean of u_x over the fluid cells of plane x = px.
-__global__ void __launch_bounds__(256)
+// Objective: mean of u_x over the fluid cells of plane x = px.  Its cells lie a
+// row apart, a line of memory for every population of each: one block's
+// work-group took 119 us for the 64 x 64 plane, so blocks of one wave sum a
+// row each and a second launch adds up their sums in order.
+constexpr int OBJ_THREADS = 64;
+constexpr int OBJ_BLOCKS = RED_BLOCKS / 2;  // at most: two doubles each
+
+__device__ __forceinline__ void wave_sum(double& a, double& b) {
+#pragma unroll
+  for (int s = OBJ_THREADS / 2; s > 0; s >>= 1) {
+    a += __shfl_down(a, s);
+    b += __shfl_down(b, s);
+  }
+}
+
+__global__ void __launch_bounds__(OBJ_THREADS)
     porous_objective_kernel(const float* __restrict__ f, const uint32_t* __restrict__ link,
-                            int px, int nx, int ny, int nz, uint32_t PS, float gx,
-                            double* __restrict__ out) {
-  __shared__ double s_sum[256];
-  __shared__ double s_cnt[256];
+                            int px, int nx, int rows, uint32_t PS, float gx,
+                            double* __restrict__ partials) {
   double sum = 0.0, cnt = 0.0;
-  for (int r = threadIdx.x; r < ny * nz; r += blockDim.x) {
+  for (int r = (int)(blockIdx.x * blockDim.x + threadIdx.x); r < rows;
+       r += (int)(gridDim.x * blockDim.x)) {
     const uint32_t idx = (uint32_t)px + (uint32_t)nx * (uint32_t)r;
+    float v[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) v[i] = f[(uint32_t)i * PS + idx];
     if (!(link[idx] & LINK_FLUID)) continue;
     double drho = 0.0, jx = 0.0;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      const double v = f[(uint32_t)i * PS + idx];
-      drho += v;
-      jx += V::cx[i] * v;
+      drho += (double)v[i];
+      jx += V::cx[i] * (double)v[i];
     }
     sum += jx / (1.0 + drho) + 0.5 * gx;
     cnt += 1.0;
   }
-  s_sum[threadIdx.x] = sum;
-  s_cnt[threadIdx.x] = cnt;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      s_sum[threadIdx.x] += s_sum[threadIdx.x + s];
-      s_cnt[threadIdx.x] += s_cnt[threadIdx.x + s];
-    }
-    __syncthreads();
-  }
+  wave_sum(sum, cnt);
   if (threadIdx.x == 0) {
-    out[0] = s_cnt[0] > 0 ? s_sum[0] / s_cnt[0] : 0.0;
-    out[1] = s_cnt[0];
+    partials[2 * blockIdx.x] = sum;
+    partials[2 * blockIdx.x + 1] = cnt;
+  }
+}
+
+// out: the mean and the number of cells
+__global__ void __launch_bounds__(OBJ_THREADS)
+    porous_objective_final_kernel(const double* __restrict__ partials, int n, double* __restrict__ out) {
+  double sum = 0.0, cnt = 0.0;
+  for (int k = (int)threadIdx.x; k < n; k += OBJ_THREADS) {
+    sum += partials[2 * k];
+    cnt += partials[2 * k + 1];
+  }
+  wave_sum(sum, cnt);
+  if (threadIdx.x == 0) {
+    out[0] = cnt > 0 ? sum / cnt : 0.0;
+    out[1] = cnt;
   }
 }
 
@@ -539,9 +560,13 @@ lbm_status lbm_porous_forward(lbm_porous* h, const float* porosity_dev, double* 
   for (int t = 0; t < h->steps; ++t) launch_step(h, state(t), state(t + 1));
   const int cur = h->steps & 1;
   double* red = (double*)(h->work + h->lay.red);
-  hipLaunchKernelGGL(porous_objective_kernel, dim3(1), dim3(256), 0, h->stream, bufs[cur],
-                     (const uint32_t*)(h->work + h->lay.link), h->plane_x, h->nx, h->ny, h->nz,
-                     (uint32_t)h->PS, h->p.g[0], red);
+  const int rows = h->ny * h->nz;
+  const int blocks = std::min((int)grid_for((size_t)rows, OBJ_THREADS), OBJ_BLOCKS);
+  hipLaunchKernelGGL(porous_objective_kernel, dim3(blocks), dim3(OBJ_THREADS), 0, h->stream,
+                     bufs[cur], (const uint32_t*)(h->work + h->lay.link), h->plane_x, h->nx, rows,
+                     (uint32_t)h->PS, h->p.g[0], red + 8);
+  hipLaunchKernelGGL(porous_objective_final_kernel, dim3(1), dim3(OBJ_THREADS), 0, h->stream,
+                     red + 8, blocks, red);
   PHIP_TRY(h, hipGetLastError());
   double r[2];
   PHIP_TRY(h, hipMemcpyAsync(r, red, sizeof(r), hipMemcpyDeviceToHost, h->stream));
@@ -567,8 +592,8 @@ lbm_status lbm_porous_backward(lbm_porous* h, float* grad_dev) {
   const size_t nstate = h->lay.state_bytes / sizeof(float);
   hipLaunchKernelGGL(fill_kernel, dim3(1024), dim3(256), 0, h->stream, lam[0], nstate, 0.f);
   hipLaunchKernelGGL(fill_kernel, dim3(1024), dim3(256), 0, h->stream, grad_dev, h->N, 0.f);
-  hipLaunchKernelGGL(porous_lambda_final_kernel, dim3(grid_for((size_t)h->ny * h->nz)), dim3(256),
-                     0, h->stream, fT, link, lam[0], h->plane_x, h->nx, h->ny, h->nz,
+  hipLaunchKernelGGL(porous_lambda_final_kernel, dim3(grid_for((size_t)h->ny * h->nz, OBJ_THREADS)),
+                     dim3(OBJ_THREADS), 0, h->stream, fT, link, lam[0], h->plane_x, h->nx, h->ny, h->nz,
                      (uint32_t)h->PS, (const double*)(h->work + h->lay.red));
   int cur = 0;  // lam[cur] holds lambda^{t+1}
   for (int k = h->lay.nckpt - 1; k >= 0; --k) {
