@@ -466,10 +466,11 @@ int launch_steps(lbm_batch* b, int n, int phase) {
 // LBM_ERR_HIP on a HIP failure.
 lbm_status enqueue_batch_steps(lbm_batch* b, int n, int* phase) {
   int left = n;
-  while (b->graph_steps > 0 && left >= b->graph_steps) {
+  // runs of fewer than eight passes of two steps are launched directly
+  const bool replay = b->graph_steps > 0 && (!b->second || b->graph_steps >= 16);
+  while (replay && left >= b->graph_steps) {
     hipGraphExec_t& exec = b->graph[*phase];
-    int end = *phase;
-    if (b->second && b->graph_steps >= 4) end = 1;  // an even run after passes
+    const int end = b->second ? 1 : *phase;  // an even run, through passes or not
     if (!exec) {
       hipGraph_t g = nullptr;
       BHIP_TRY(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));

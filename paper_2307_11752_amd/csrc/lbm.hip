@@ -1061,11 +1061,15 @@ int launch_steps(lbm_lattice* h, const OpTable& t, int n, int phase, long long n
 lbm_status enqueue_steps(lbm_lattice* h, int n) {
   const OpTable t = ops(h);
   int left = n;
-  while (h->graph_steps > 0 && left >= h->graph_steps) {
+  // Runs of fewer than eight passes are launched directly: cut into replays
+  // they would be shorter passes, and single steps between them (341^2 BF16
+  // cavity over 32 steps: replays of two 366 us, directly 68 us).
+  const int pass = !h->second ? 0 : (h->deep.use ? h->deep.steps : (h->pair.use ? 2 : 0));
+  const bool replay = h->graph_steps > 0 && h->graph_steps >= 8 * pass;
+  while (replay && left >= h->graph_steps) {
     // the phase a run of this length ends in (its length is even: the phase it
-    // starts in, unless it takes passes of two steps)
-    const bool pairs = (h->pair.use || h->deep.use) && h->second && h->graph_steps >= 4;
-    const int end = pairs ? 1 : h->phase;
+    // starts in, unless it takes passes)
+    const int end = pass ? 1 : h->phase;
     const long long number = h->steps + (n - left);
     hipGraphExec_t& exec = h->graph[2 * (number & 1) + h->phase];
     if (!exec) {
