@@ -171,15 +171,18 @@ __global__ void __launch_bounds__(256)
                        int ny, int nz, uint32_t N, uint32_t PS, PorousParams p) {
   const uint32_t idx = xcd_run_block() * blockDim.x + threadIdx.x;
   if (idx >= N) return;
+  // the loads do not wait for the link word
   const uint32_t lw = link[idx];
+  const float d = por[idx];
+  float f[Q], out[Q];
+#pragma unroll
+  for (int i = 0; i < Q; ++i) f[i] = src[(uint32_t)i * PS + idx];
+  __builtin_amdgcn_sched_barrier(0);
   if (!(lw & LINK_FLUID)) return;
   const int x = (int)(idx % (uint32_t)nx);
   const int r = (int)(idx / (uint32_t)nx);
   const Nbr nb = make_nbr(x, r % ny, r / ny, nx, ny, nz);
-  float f[Q], out[Q];
-#pragma unroll
-  for (int i = 0; i < Q; ++i) f[i] = src[(uint32_t)i * PS + idx];
-  porous_collide_cell(f, por[idx], p, out);
+  porous_collide_cell(f, d, p, out);
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     const bool wall = i > 0 && ((lw >> (i - 1)) & 1u);
@@ -261,25 +264,30 @@ __global__ void __launch_bounds__(256)
                           int nx, int ny, int nz, uint32_t N, uint32_t PS, PorousParams p) {
   const uint32_t idx = xcd_run_block() * blockDim.x + threadIdx.x;
   if (idx >= N) return;
+  // the loads do not wait for the link word; what a wall reflects is loaded after it
   const uint32_t lw = link[idx];
-  if (!(lw & LINK_FLUID)) {
-#pragma unroll
-    for (int i = 0; i < Q; ++i) lam_cur[(uint32_t)i * PS + idx] = 0.f;
-    return;
-  }
+  const float d = por[idx], g = grad[idx];
   const int x = (int)(idx % (uint32_t)nx);
   const int r = (int)(idx / (uint32_t)nx);
   const Nbr nb = make_nbr(x, r % ny, r / ny, nx, ny, nz);
   float mu[Q], f[Q], lam[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
-    const bool wall = i > 0 && ((lw >> (i - 1)) & 1u);
-    const uint32_t off = wall ? (uint32_t)V::opp[i] * PS + idx
-                              : (uint32_t)i * PS + nb.at(V::cx[i], V::cy[i], V::cz[i]);
-    mu[i] = lam_next[off];
+    mu[i] = lam_next[(uint32_t)i * PS + nb.at(V::cx[i], V::cy[i], V::cz[i])];
     f[i] = f_t[(uint32_t)i * PS + idx];
   }
-  grad[idx] += porous_adjoint_cell(f, mu, por[idx], p, lam);
+  __builtin_amdgcn_sched_barrier(0);
+  if (!(lw & LINK_FLUID)) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) lam_cur[(uint32_t)i * PS + idx] = 0.f;
+    return;
+  }
+  if (lw != LINK_FLUID) {
+#pragma unroll
+    for (int i = 1; i < Q; ++i)
+      if ((lw >> (i - 1)) & 1u) mu[i] = lam_next[(uint32_t)V::opp[i] * PS + idx];
+  }
+  grad[idx] = g + porous_adjoint_cell(f, mu, d, p, lam);
 #pragma unroll
   for (int i = 0; i < Q; ++i) lam_cur[(uint32_t)i * PS + idx] = lam[i];
 }
