@@ -162,12 +162,16 @@ lbm_status lbm_get_populations(lbm_lattice* h, double* f_dev);
 
 /* Advance n >= 0 full time steps (collide + stream), enqueued on the lattice's
  * stream.  async.  After the call the stored state is the post-streaming,
- * pre-collision population set at time t0 + n. */
+ * pre-collision population set at time t0 + n.  Captured into a graph of the
+ * caller's, an even n leaves the propagation phase it began in, so that the
+ * graph can be replayed. */
 lbm_status lbm_step(lbm_lattice* h, int n);
 
 /* Replay lbm_step in captured HIP graphs of `steps` time steps (even, > 0;
  * 0 = direct launches, the default).  lbm_step(n) then launches whole graphs
- * for as many full runs of `steps` as n holds and the rest directly.  Needs a
+ * for as many full runs of `steps` as n holds and the rest directly; a lattice
+ * that takes several steps to a pass launches runs of fewer than eight passes
+ * directly.  Needs a
  * non-null stream (graph capture); the graph is rebuilt after any change of
  * tau, force, wall velocity or geometry.  Results are identical to direct
  * launches (same kernels, same arguments). */

@@ -88,7 +88,7 @@ __global__ void __launch_bounds__(512)
       // lane that runs past the last cell only touches padding slots (the
       // population runs are padded to a multiple of 64 cells or whole chunks)
       const uint32_t c0 = item.first + (uint32_t)CM * threadIdx.x;
-      if (c0 < item.first + item.count) fluid_cells_p0<Q, S, SHIFT, CM>(pop, L.pix, c0, p);
+      if (c0 < item.first + item.count) fluid_cells_p0<Q, S, SHIFT, CM, sizeof(S) == 2>(pop, L.pix, c0, p);
     } else {
       const int rloc = (int)threadIdx.x / L.tpr;
       const int t = (int)threadIdx.x - rloc * L.tpr;
@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(512)
       // only 16-bit members have padded rows (member_pitch).  FP32 rows load
       // through the caches (measured: ensemble phase 1 755 -> 721 us; 16-bit
       // storage gains nothing, and the single lattice's 256-cell rows lose)
-      fluid_rows_p1<Q, S, SHIFT, LC, sizeof(S) == 2, sizeof(S) != 4>(
+      fluid_rows_p1<Q, S, SHIFT, LC, sizeof(S) == 2, sizeof(S) != 4, sizeof(S) == 2>(
           pop, L.nx, L.px, L.ny, L.nz, L.pix, row, active, t, tile, p);
       __syncthreads();  // the next item reuses the LDS tile
     }
@@ -446,8 +446,8 @@ void launch_pair(lbm_batch* b, bool to_second, bool entry) {
 
 // Launch n steps from propagation phase `phase`; returns the phase they end
 // in.  Fours of steps run as two passes, there and back (leaving phase 1).
-int launch_steps(lbm_batch* b, int n, int phase) {
-  if (b->second) {
+int launch_steps(lbm_batch* b, int n, int phase, bool passes) {
+  if (passes && b->second) {
     for (; n >= 4; n -= 4) {
       launch_pair(b, true, phase == 0);
       launch_pair(b, false, false);
@@ -466,15 +466,17 @@ int launch_steps(lbm_batch* b, int n, int phase) {
 // LBM_ERR_HIP on a HIP failure.
 lbm_status enqueue_batch_steps(lbm_batch* b, int n, int* phase) {
   int left = n;
+  // single steps in a graph that a caller captures: see lbm_step
+  const bool passes = n < 4 || !lbm_detail::captured(b->stream);
   // runs of fewer than eight passes of two steps are launched directly
-  const bool replay = b->graph_steps > 0 && (!b->second || b->graph_steps >= 16);
+  const bool replay = b->graph_steps > 0 && (!b->second || !passes || b->graph_steps >= 16);
   while (replay && left >= b->graph_steps) {
     hipGraphExec_t& exec = b->graph[*phase];
     const int end = b->second ? 1 : *phase;  // an even run, through passes or not
     if (!exec) {
       hipGraph_t g = nullptr;
       BHIP_TRY(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-      (void)launch_steps(b, b->graph_steps, *phase);
+      (void)launch_steps(b, b->graph_steps, *phase, true);
       hipError_t e = hipStreamEndCapture(b->stream, &g);
       if (e != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -491,7 +493,7 @@ lbm_status enqueue_batch_steps(lbm_batch* b, int n, int* phase) {
     left -= b->graph_steps;
     *phase = end;
   }
-  *phase = launch_steps(b, left, *phase);
+  *phase = launch_steps(b, left, *phase, passes);
   return LBM_OK;
 }
 

@@ -87,7 +87,7 @@ struct Shifted {
 // Phase 0 of cells c0 .. c0+C-1 (all fluid): read own slots, collide, write
 // f*_i into slot opp(i).  L places the populations (C consecutive cells of a
 // population are adjacent: c0 % C == 0 and C divides the chunk size).
-template <int Q, typename S, bool SHIFT, int C>
+template <int Q, typename S, bool SHIFT, int C, bool FREE = false>
 __device__ __forceinline__ void fluid_cells_p0(S* __restrict__ pop, const PopIndex& L, uint32_t c0,
                                                const StepParams<typename Store<S>::T>& p) {
   using T = typename Store<S>::T;
@@ -104,7 +104,7 @@ __device__ __forceinline__ void fluid_cells_p0(S* __restrict__ pop, const PopInd
     T f[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) f[i] = Store<S>::cvt(sv[i][k]);
-    collide<Q, SHIFT, T>(f, p);
+    collide_as<FREE, Q, SHIFT, T>(f, p);
 #pragma unroll
     for (int i = 0; i < Q; ++i) sv[V::opp[i]][k] = Store<S>::pack(f[i]);
     __builtin_amdgcn_sched_barrier(0);
@@ -122,7 +122,8 @@ __device__ __forceinline__ void fluid_cells_p0(S* __restrict__ pop, const PopInd
 // NT_LOADS = false reads through the caches (for rows that share lines with
 // their neighbours, as short rows do).  Contains block barriers: every thread
 // of the block must call it (inactive lanes with active = false).
-template <int Q, typename S, bool SHIFT, int C, bool PADDED = false, bool NT_LOADS = true>
+template <int Q, typename S, bool SHIFT, int C, bool PADDED = false, bool NT_LOADS = true,
+          bool FREE = false>
 __device__ __forceinline__ void fluid_rows_p1(S* __restrict__ pop, int nx, int px, int ny, int nz,
                                               const PopIndex& L, int row, bool active, int t, S* tile,
                                               const StepParams<typename Store<S>::T>& p) {
@@ -166,7 +167,7 @@ __device__ __forceinline__ void fluid_rows_p1(S* __restrict__ pop, int nx, int p
       T f[Q];
 #pragma unroll
       for (int i = 0; i < Q; ++i) f[i] = Store<S>::cvt(sv[i][k]);
-      collide<Q, SHIFT, T>(f, p);
+      collide_as<FREE, Q, SHIFT, T>(f, p);
 #pragma unroll
       for (int i = 0; i < Q; ++i) sv[i][k] = Store<S>::pack(f[i]);
     }
@@ -243,7 +244,7 @@ __device__ __forceinline__ void shift_along_row(S (&v)[C], int s, int left, int 
 // storing, so no LDS tile and no barrier is needed.  A row must not straddle
 // two chunks of L (nx divides the chunk size), so that a row's slots are
 // addressed from the row start plus x.
-template <int Q, typename S, bool SHIFT, int C>
+template <int Q, typename S, bool SHIFT, int C, bool FREE = false>
 __device__ __forceinline__ void fluid_rows_p1_wave(S* __restrict__ pop, int nx, int ny, int nz,
                                                    const PopIndex& L, int row, int t, int left,
                                                    int right,
@@ -273,7 +274,7 @@ __device__ __forceinline__ void fluid_rows_p1_wave(S* __restrict__ pop, int nx, 
     T f[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) f[i] = Store<S>::cvt(sv[i][k]);
-    collide<Q, SHIFT, T>(f, p);
+    collide_as<FREE, Q, SHIFT, T>(f, p);
 #pragma unroll
     for (int i = 0; i < Q; ++i) sv[i][k] = Store<S>::pack(f[i]);
     // one cell at a time: interleaving the C collisions only raises register

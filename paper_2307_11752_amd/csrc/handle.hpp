@@ -150,6 +150,11 @@ struct lbm_lattice {
 
 
 namespace lbm_detail {
+// A caller is capturing this stream into a graph of its own.
+inline bool captured(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return stream && hipStreamIsCapturing(stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
 lbm_status fail(lbm_lattice* h, lbm_status st, const std::string& msg);
 void drop_graph(lbm_lattice* h);
 // lbm_lattice_create with an explicit scratch area: own_scratch bytes of the

@@ -204,7 +204,7 @@ struct StepParams {
   T mw[19];     // 6 w_i (c_i . u_w): moving-wall momentum term per unit density
   int has_force;
   int has_moving;
-  int fused_u;  // bit 0: step taken (first of two), bit 1: second of two; see collide
+  int fused_u;  // bit 0: the launch's first step (third, ...), bit 1: its second; see collide
 };
 
 // Velocity i + H (H = (Q - 1) / 2) is the opposite of velocity i for
@@ -371,6 +371,73 @@ __device__ __forceinline__ T collide(T (&f)[Q], const StepParams<T>& p, bool fus
     });
   }
   return rho;
+}
+
+// The same collision with the fused operations left to the compiler, for 16-bit
+// lattices and batches that take no passes: their stored values, and so every
+// later bit, are those of the library before it had passes, and a step with
+// walls is 0.8 % faster than with both roundings of u at hand (channel
+// 512 x 128 x 128 FP16, 20 steps and a field read: 2500 against 2520 us).
+template <int Q, bool SHIFT, typename T>
+__device__ __forceinline__ T collide_free(T (&f)[Q], const StepParams<T>& p) {
+  using V = Vel<Q>;
+  constexpr int H = (Q - 1) / 2;
+  static_assert(pairs_are_opposite<Q>(), "velocity i + H must be the opposite of velocity i");
+  T sf = f[0], jx = T(0), jy = T(0), jz = T(0);
+  bool fx = true, fy = true, fz = true;
+  static_for<1, H + 1>([&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    const T d = f[k] - f[k + H];
+    sf += f[k] + f[k + H];
+    accumulate<V::cx[k]>(jx, fx, d);
+    accumulate<V::cy[k]>(jy, fy, d);
+    accumulate<V::cz[k]>(jz, fz, d);
+  });
+  const T rho = SHIFT ? p.base + sf : sf;
+  const T inv = reciprocal(rho);
+  T ux = jx * inv, uy = jy * inv, uz = V::D == 3 ? jz * inv : T(0);
+  if (p.has_force) {
+    ux += T(0.5) * p.g[0];
+    uy += T(0.5) * p.g[1];
+    if (V::D == 3) uz += T(0.5) * p.g[2];
+  }
+  const T uu = V::D == 3 ? ux * ux + uy * uy + uz * uz : ux * ux + uy * uy;
+  const T A = sf - T(1.5) * rho * uu;
+  const T om = p.omega;
+  f[0] = fma(om, weight<Q, T>(0) * A - f[0], f[0]);
+  static_for<1, H + 1>([&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    const T w = weight<Q, T>(k);
+    const T cu = cdot<V::cx[k], V::cy[k], V::cz[k]>(ux, uy, uz);
+    const T rc = rho * cu;
+    const T P = w * fma(T(4.5) * rc, cu, A);
+    const T M = w * (T(3) * rc);
+    f[k] = fma(om, (P + M) - f[k], f[k]);
+    f[k + H] = fma(om, (P - M) - f[k + H], f[k + H]);
+  });
+  if (p.has_force) {
+    const T Fx = rho * p.g[0], Fy = rho * p.g[1], Fz = V::D == 3 ? rho * p.g[2] : T(0);
+    const T uF = V::D == 3 ? ux * Fx + uy * Fy + uz * Fz : ux * Fx + uy * Fy;
+    const T kg = p.kguo;
+    f[0] += kg * weight<Q, T>(0) * (T(-3) * uF);
+    static_for<1, H + 1>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      const T kw = kg * weight<Q, T>(k);
+      const T cu = cdot<V::cx[k], V::cy[k], V::cz[k]>(ux, uy, uz);
+      const T cF = cdot<V::cx[k], V::cy[k], V::cz[k]>(Fx, Fy, Fz);
+      const T GP = kw * fma(T(9) * cu, cF, T(-3) * uF);
+      const T GM = kw * (T(3) * cF);
+      f[k] += GP + GM;
+      f[k + H] += GP - GM;
+    });
+  }
+  return rho;
+}
+
+template <bool FREE, int Q, bool SHIFT, typename T>
+__device__ __forceinline__ T collide_as(T (&f)[Q], const StepParams<T>& p, bool fused_u = false) {
+  if constexpr (FREE) return collide_free<Q, SHIFT, T>(f, p);
+  return collide<Q, SHIFT, T>(f, p, fused_u);
 }
 
 // Population v reflected by a moving wall, mw = 6 w_i (c_i . u_w).

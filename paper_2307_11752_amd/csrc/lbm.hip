@@ -2,8 +2,9 @@
 // collide-and-stream step with bounce-back walls, moving walls, periodic wrap
 // and Guo forcing.
 //
-// Propagation: in-place AA pattern on one population
-// buffer.  The stream equation of the guide (f_i(t+1, x+c_i) = f*_i(t, x),
+// Propagation: runs of steps go several steps to a pass between two population
+// buffers (pair_path.hpp, deep.hip); the steps that are left, and lattices
+// without the second buffer, in place by the AA pattern.  The stream equation of the guide (f_i(t+1, x+c_i) = f*_i(t, x),
 // Introduction, "Lattice Boltzmann Methods") is realised without a second
 // lattice by alternating two kernels:
 //
@@ -79,8 +80,9 @@ struct RawReg<double> {
 // The fused step kernel.  One thread per cell; a block covers a run of up to
 // blockDim.x cells along x of one (y, z) row.
 //   MASKED = false: every cell is fluid (fully periodic box); no link words.
+//   FREE (here and below): the collision's rounding is the compiler's choice.
 // ---------------------------------------------------------------------------
-template <int Q, typename S, bool SHIFT, int PHASE, bool MASKED>
+template <int Q, typename S, bool SHIFT, int PHASE, bool MASKED, bool FREE = false>
 __global__ void __launch_bounds__(256)
     step_kernel(S* __restrict__ pop, const uint32_t* __restrict__ link,
                 const uint32_t* __restrict__ mov, int nx, int ny, int nz, PopIndex L, int nxb,
@@ -170,7 +172,7 @@ __global__ void __launch_bounds__(256)
     }
   }
 
-  const T rho = collide<Q, SHIFT, T>(f, p, MASKED && (p.fused_u & 1));
+  const T rho = collide_as<FREE, Q, SHIFT, T>(f, p, MASKED && (p.fused_u & 1));
 
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
@@ -202,7 +204,7 @@ __global__ void __launch_bounds__(256)
 // LDS and stored aligned.  This removes the misaligned accesses that
 // otherwise cost about 12 % of bandwidth in this phase.
 // ---------------------------------------------------------------------------
-template <int Q, typename S, bool SHIFT, int C>
+template <int Q, typename S, bool SHIFT, int C, bool FREE>
 __global__ void __launch_bounds__(256)
     step_p0_flat_kernel(S* __restrict__ pop, uint32_t N, PopIndex L,
                         StepParams<typename Store<S>::T> p) {
@@ -211,10 +213,10 @@ __global__ void __launch_bounds__(256)
   const unsigned bid = sizeof(S) == 4 ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
   const uint32_t c0 = (uint32_t)C * (bid * blockDim.x + threadIdx.x);
   if (c0 >= N) return;
-  fluid_cells_p0<Q, S, SHIFT, C>(pop, L, c0, p);
+  fluid_cells_p0<Q, S, SHIFT, C, FREE>(pop, L, c0, p);
 }
 
-template <int Q, typename S, bool SHIFT>
+template <int Q, typename S, bool SHIFT, bool FREE>
 __global__ void __launch_bounds__(256)
     step_p1_rows_kernel(S* __restrict__ pop, int nx, int ny, int nz, PopIndex L, int tpr,
                         int rows_per_block, StepParams<typename Store<S>::T> p) {
@@ -224,7 +226,7 @@ __global__ void __launch_bounds__(256)
   const int t = (int)threadIdx.x - rloc * tpr;
   const int row = (int)blockIdx.x * rows_per_block + rloc;
   S* tile = (S*)smem_raw + (size_t)rloc * Shifted<Q>::count() * nx;
-  fluid_rows_p1<Q, S, SHIFT, C>(pop, nx, nx, ny, nz, L, row, row < ny * nz, t, tile, p);
+  fluid_rows_p1<Q, S, SHIFT, C, false, true, FREE>(pop, nx, nx, ny, nz, L, row, row < ny * nz, t, tile, p);
 }
 
 // Phase 1 with each x-row held by 2^lr_log2 = nx / C lanes of one wave (a
@@ -232,7 +234,7 @@ __global__ void __launch_bounds__(256)
 // and no barrier: the x-shifted populations move between lanes in registers.
 // ONE_ROW (nx = 64 C): the wave's row is uniform, so every row address is
 // scalar and the lanes only carry their x offset.
-template <int Q, typename S, bool SHIFT, int C, bool ONE_ROW>
+template <int Q, typename S, bool SHIFT, int C, bool ONE_ROW, bool FREE>
 __global__ void __launch_bounds__(256)
     step_p1_wave_kernel(S* __restrict__ pop, int nx, int ny, int nz, PopIndex L, int lr_log2,
                         StepParams<typename Store<S>::T> p) {
@@ -241,7 +243,7 @@ __global__ void __launch_bounds__(256)
   if constexpr (ONE_ROW) {
     const int row = __builtin_amdgcn_readfirstlane(wave);
     if (row >= ny * nz) return;
-    fluid_rows_p1_wave<Q, S, SHIFT, C>(pop, nx, ny, nz, L, row, lane, (lane - 1) & 63,
+    fluid_rows_p1_wave<Q, S, SHIFT, C, FREE>(pop, nx, ny, nz, L, row, lane, (lane - 1) & 63,
                                        (lane + 1) & 63, p);
   } else {
     const int lr = 1 << lr_log2;
@@ -249,7 +251,7 @@ __global__ void __launch_bounds__(256)
     const int first = lane - t;
     const int row = (wave << (6 - lr_log2)) + (lane >> lr_log2);
     if (row >= ny * nz) return;  // whole rows drop out together
-    fluid_rows_p1_wave<Q, S, SHIFT, C>(pop, nx, ny, nz, L, row, t, first + ((t - 1) & (lr - 1)),
+    fluid_rows_p1_wave<Q, S, SHIFT, C, FREE>(pop, nx, ny, nz, L, row, t, first + ((t - 1) & (lr - 1)),
                                        first + ((t + 1) & (lr - 1)), p);
   }
 }
@@ -283,7 +285,7 @@ struct ClassVec {
   }
 };
 
-template <int Q, typename S, bool SHIFT>
+template <int Q, typename S, bool SHIFT, bool FREE>
 __global__ void __launch_bounds__(256)
     step_p0_masked_kernel(S* __restrict__ pop, const uint8_t* __restrict__ cls,
                           const uint32_t* __restrict__ mov, uint32_t N, PopIndex L,
@@ -310,7 +312,7 @@ __global__ void __launch_bounds__(256)
     T f[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) f[i] = Store<S>::cvt(sv[i][k]);
-    const T rho = collide<Q, SHIFT, T>(f, p, p.fused_u & 1);
+    const T rho = collide_as<FREE, Q, SHIFT, T>(f, p, p.fused_u & 1);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       T v = f[i];
@@ -758,6 +760,7 @@ template <int Q, typename S, bool SHIFT>
 struct Ops {
   using T = typename Store<S>::T;
 
+  template <bool FREE>
   static void launch_p1_wave(lbm_lattice* h, S* pop, PopIndex L, int lrw, const StepParams<T>& p) {
     if constexpr (sizeof(S) == 2) {
       constexpr int C = Pack8<S>::C;
@@ -767,15 +770,21 @@ struct Ops {
       const size_t waves = (rows + (64 >> lrw) - 1) / (64 >> lrw);
       const unsigned nb = (unsigned)((waves * 64 + threads - 1) / threads);
       if (lrw == 6)
-        hipLaunchKernelGGL((step_p1_wave_kernel<Q, S, SHIFT, C, true>), dim3(nb), dim3(threads), lds,
+        hipLaunchKernelGGL((step_p1_wave_kernel<Q, S, SHIFT, C, true, FREE>), dim3(nb), dim3(threads), lds,
                            h->stream, pop, h->nx, h->ny, h->nz, L, lrw, p);
       else
-        hipLaunchKernelGGL((step_p1_wave_kernel<Q, S, SHIFT, C, false>), dim3(nb), dim3(threads),
+        hipLaunchKernelGGL((step_p1_wave_kernel<Q, S, SHIFT, C, false, FREE>), dim3(nb), dim3(threads),
                            lds, h->stream, pop, h->nx, h->ny, h->nz, L, lrw, p);
     }
   }
 
   static void step(lbm_lattice* h, int phase, long long number) {
+    const bool passes = h->pair.use || h->deep.use;
+    sizeof(S) == 2 && !passes ? step_as<sizeof(S) == 2>(h, phase, number) : step_as<false>(h, phase, number);
+  }
+
+  template <bool FREE>
+  static void step_as(lbm_lattice* h, int phase, long long number) {
     StepParams<T> p = make_params<T>(h, number);
     p.base = (T)Store<S>::unit;
     S* pop = (S*)h->pop;
@@ -799,7 +808,7 @@ struct Ops {
       constexpr int C0 = sizeof(S) == 2 ? 2 : C;
       const unsigned threads = sizeof(S) == 2 ? 256 : 128;
       const unsigned nb = (unsigned)(((h->N + C0 - 1) / C0 + threads - 1) / threads);
-      hipLaunchKernelGGL((step_p0_flat_kernel<Q, S, SHIFT, C0>), dim3(nb), dim3(threads),
+      hipLaunchKernelGGL((step_p0_flat_kernel<Q, S, SHIFT, C0, FREE>), dim3(nb), dim3(threads),
                          occupancy_lds(h, sizeof(S) == 2 ? 6 : 4, 0), h->stream, pop, N, L, p);
     } else if (h->all_fluid && (lrw >= 0 || (h->nx % C == 0 && tpr <= 256))) {
       // phase 1 on whole rows, one wave per row for 16-bit storage (128
@@ -807,13 +816,13 @@ struct Ops {
       // whole rows, about 128 threads and four blocks per CU; rows wider than
       // 128 lanes one per block, three blocks per CU)
       if (lrw >= 0) {
-        launch_p1_wave(h, pop, L, lrw, p);
+        launch_p1_wave<FREE>(h, pop, L, lrw, p);
       } else {
         const int rpb = tpr >= 128 ? 1 : 128 / tpr;
         const int rows = h->ny * h->nz;
         const unsigned nb = (unsigned)((rows + rpb - 1) / rpb);
         const size_t lds = (size_t)rpb * Shifted<Q>::count() * h->nx * sizeof(S);
-        hipLaunchKernelGGL((step_p1_rows_kernel<Q, S, SHIFT>), dim3(nb), dim3(rpb * tpr),
+        hipLaunchKernelGGL((step_p1_rows_kernel<Q, S, SHIFT, FREE>), dim3(nb), dim3(rpb * tpr),
                            occupancy_lds(h, rpb * tpr <= 128 ? 4 : 3, lds), h->stream, pop, h->nx,
                            h->ny, h->nz, L, tpr, rpb, p);
       }
@@ -822,18 +831,18 @@ struct Ops {
       // 4- and 8-byte storage (measured); 16-bit storage gains nothing from a cap.
       const unsigned threads = 128;
       const unsigned nb = (unsigned)((h->N / C + threads - 1) / threads);
-      hipLaunchKernelGGL((step_p0_masked_kernel<Q, S, SHIFT>), dim3(nb), dim3(threads),
+      hipLaunchKernelGGL((step_p0_masked_kernel<Q, S, SHIFT, FREE>), dim3(nb), dim3(threads),
                          occupancy_lds(h, sizeof(S) >= 4 ? 6 : 0, 0), h->stream, pop,
                          (const uint8_t*)(h->aux + h->lay.cls), mov, N, L, p);
     } else if (h->all_fluid) {  // phase 1, rows the row kernels do not take
-      hipLaunchKernelGGL((step_kernel<Q, S, SHIFT, 1, false>), grid, block, 0, h->stream, pop,
+      hipLaunchKernelGGL((step_kernel<Q, S, SHIFT, 1, false, FREE>), grid, block, 0, h->stream, pop,
                          link, mov, h->nx, h->ny, h->nz, L, h->nxb, p);
     } else {
       if (phase == 0)
-        hipLaunchKernelGGL((step_kernel<Q, S, SHIFT, 0, true>), grid, block, 0, h->stream, pop,
+        hipLaunchKernelGGL((step_kernel<Q, S, SHIFT, 0, true, FREE>), grid, block, 0, h->stream, pop,
                            link, mov, h->nx, h->ny, h->nz, L, h->nxb, p);
       else
-        hipLaunchKernelGGL((step_kernel<Q, S, SHIFT, 1, true>), grid, block, 0, h->stream, pop,
+        hipLaunchKernelGGL((step_kernel<Q, S, SHIFT, 1, true, FREE>), grid, block, 0, h->stream, pop,
                            link, mov, h->nx, h->ny, h->nz, L, h->nxb, p);
     }
   }
@@ -1030,8 +1039,8 @@ lbm_status reduce_totals(lbm_lattice* h, double* partials, double* result, doubl
 // buffers and leave phase 1: D2Q9 an even number of about equal ones from four
 // steps on, D3Q19 two of two steps for every four.  Other steps run one by one
 // in place.
-int launch_steps(lbm_lattice* h, const OpTable& t, int n, int phase, long long number) {
-  if (h->deep.use && h->second && n >= 4) {
+int launch_steps(lbm_lattice* h, const OpTable& t, int n, int phase, long long number, bool passes) {
+  if (passes && h->deep.use && h->second && n >= 4) {
     for (int left = (n + 2 * h->deep.steps - 1) / (2 * h->deep.steps) * 2; left > 0; --left) {
       const int k = (n + left - 1) / left;
       t.deep(h, left % 2 == 0 ? h->pop : h->second, left % 2 == 0 ? h->second : h->pop, k, phase == 0,
@@ -1042,7 +1051,7 @@ int launch_steps(lbm_lattice* h, const OpTable& t, int n, int phase, long long n
     }
     return phase;
   }
-  if (h->pair.use && h->second) {
+  if (passes && h->pair.use && h->second) {
     for (; n >= 4; n -= 4, number += 4) {
       t.pair(h, h->pop, h->second, phase == 0, number);
       t.pair(h, h->second, h->pop, false, number + 2);
@@ -1061,10 +1070,13 @@ int launch_steps(lbm_lattice* h, const OpTable& t, int n, int phase, long long n
 lbm_status enqueue_steps(lbm_lattice* h, int n) {
   const OpTable t = ops(h);
   int left = n;
+  // A caller's own graph is replayed from the phase it was captured in: single
+  // steps, an even number of which returns to it.  (Passes always end in phase 1.)
+  const bool passes = n < 4 || !lbm_detail::captured(h->stream);
   // Runs of fewer than eight passes are launched directly: cut into replays
   // they would be shorter passes, and single steps between them (341^2 BF16
   // cavity over 32 steps: replays of two 366 us, directly 68 us).
-  const int pass = !h->second ? 0 : (h->deep.use ? h->deep.steps : (h->pair.use ? 2 : 0));
+  const int pass = !h->second || !passes ? 0 : (h->deep.use ? h->deep.steps : (h->pair.use ? 2 : 0));
   const bool replay = h->graph_steps > 0 && h->graph_steps >= 8 * pass;
   while (replay && left >= h->graph_steps) {
     // the phase a run of this length ends in (its length is even: the phase it
@@ -1075,7 +1087,7 @@ lbm_status enqueue_steps(lbm_lattice* h, int n) {
     if (!exec) {
       hipGraph_t g = nullptr;
       HIP_TRY(h, hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-      (void)launch_steps(h, t, h->graph_steps, h->phase, number);
+      (void)launch_steps(h, t, h->graph_steps, h->phase, number, true);
       hipError_t e = hipStreamEndCapture(h->stream, &g);
       if (e != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -1092,7 +1104,7 @@ lbm_status enqueue_steps(lbm_lattice* h, int n) {
     left -= h->graph_steps;
     h->phase = end;
   }
-  h->phase = launch_steps(h, t, left, h->phase, h->steps + (n - left));
+  h->phase = launch_steps(h, t, left, h->phase, h->steps + (n - left), passes);
   return LBM_OK;
 }
 
@@ -1251,9 +1263,12 @@ lbm_status lbm_set_geometry(lbm_lattice* h, const uint8_t* material, unsigned pe
   h->all_fluid = (size_t)nf == h->N;
   h->pair = PairPlan{};
   h->deep = DeepPlan{};
-  if (h->second && h->q == 9)
+  // not for members of a batch; made also where the aux buffer has no room for
+  // the second buffer, as a step's rounding depends on it
+  const bool plan = h->lay.total_with_second > h->lay.second && h->scratch == h->aux + h->lay.scratch;
+  if (plan && h->q == 9)
     h->deep = lbm_detail::make_deep_plan(h->nx, h->ny, storage_bytes(h->storage), h->num_cu);
-  else if (h->second)
+  else if (plan)
     h->pair = lbm_detail::make_pair_plan(h->nx, h->ny, h->nz, storage_bytes(h->storage),
                                          !h->all_fluid, h->pix, h->num_cu);
   h->has_geometry = true;

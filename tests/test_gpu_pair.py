@@ -143,3 +143,38 @@ def test_deep_passes_equal_single_steps(lbm, shape, storage, walls):
         a, b = run.get_populations(), one.get_populations()
         assert torch.equal(a, b), int((a != b).sum())
     assert run.info()[0] == 59
+
+
+# A caller's own graph of an even number of steps returns to the phase it was
+# captured in, and can be replayed any number of times.
+@pytest.mark.parametrize("kind", ["box", "walls", "plane", "batch"])
+def test_captured_steps_replay(lbm, kind):
+    print(f"[pair] captured {kind}", flush=True)
+    shape = (40, 24, 1) if kind == "plane" else (40, 24, 12)
+    d, walls = int(kind != "plane"), kind in ("walls", "plane")
+    stream = torch.cuda.Stream()
+
+    def make():
+        if kind == "batch":
+            b = lbm.Batch(1, [shape, (16, 9, 7)], [0.7, 0.8], stream=stream)
+            for m, s in zip(b, [shape, (16, 9, 7)]):
+                m.init_equilibrium(None, W.random_velocity(s, 3, dim=3))
+            return b, list(b)
+        lat = lbm.Lattice(d, shape, 0.7, stream=stream)
+        lat.set_geometry(W.random_geometry(d, shape, 1, seed=5) if walls
+                         else np.ones(shape[::-1], np.uint8), 0b001 if walls else 0b111)
+        lat.init_equilibrium(None, W.random_velocity(shape, 3, dim=3 if d else 2))
+        return lat, [lat]
+
+    (run, states), (eager, expect) = make(), make()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        run.step(6)
+    for _ in range(3):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        torch.cuda.synchronize()
+        eager.step(6)
+        for a, b in zip(states, expect):
+            assert torch.equal(a.get_populations(), b.get_populations())
