@@ -34,7 +34,8 @@ KERNEL_SOURCES = {
                                                   "pair_path.hpp", "pair_plan.hip", "deep.hip",
                                                   "deep.hpp", "deep_plan.hip")] + ["include/lbm.h"],
     "batch": [os.path.join(_CSRC, n) for n in ("batch.hip", "lattice.hpp", "fluid_path.hpp",
-                                                "handle.hpp")] + ["include/lbm.h"],
+                                                "handle.hpp", "pair.hip", "pair.hpp",
+                                                "pair_path.hpp", "pair_plan.hip")] + ["include/lbm.h"],
     "porous": [os.path.join(_CSRC, n) for n in ("adjoint.hip", "lattice.hpp", "handle.hpp")]
     + ["include/lbm.h"],
 }
@@ -338,7 +339,9 @@ def bench_ensemble(args):
     kernel_ms = ev0.elapsed_time(ev1) / max(args.steps, 1)
     sb = STORE_BYTES[storage]
     alg_bytes = cells * 2 * 19 * sb
-    achieved = alg_bytes / (kernel_ms * 1e-3) / 1e9
+    # FP64 and FP32: launches of two steps, which read and write each population once
+    per_launch = 2 if sb > 2 else 1
+    achieved = alg_bytes / (per_launch * kernel_ms * 1e-3) / 1e9
     mlups = cells * args.steps / wall / 1e6
 
     shapes_used = {f"phase{ph}": dict(zip(("threads", "blocks_per_cu"), batch.phase_launch(ph)))
@@ -393,7 +396,9 @@ def bench_ensemble(args):
                      "traffic": measured_traffic(
                          f"ensemble/{storage}{'-shifted' if shifted else ''}", "batch"),
                      "algorithmic_bytes_per_launch": alg_bytes,
-                     "kernel": f"batch_step_kernel<Q=19,{storage}> phase 0 (one launch) + phase 1 "
+                     "kernel": f"pair_batch_kernel<Q=19,{storage}>, two steps per launch"
+                               if per_launch == 2 else
+                               f"batch_step_kernel<Q=19,{storage}> phase 0 (one launch) + phase 1 "
                                "(one launch per lane width), alternating, averaged over both"},
         "cpu_baseline": cpu,
         "oracle_parity": parity,
@@ -609,7 +614,17 @@ def main():
              for v in (args.variants or "").split(",") if v.strip()}
     _, nfluid = lat.info()
     masked = nfluid != N
+    def steps_per_launch(st):
+        """Steps of the launch that a run of many takes (the library's rule for these
+        workloads; D2Q9 passes take a number that depends on the lattice)."""
+        wide = STORE_BYTES[st] > 2 or (N <= 1100000 if masked else N >= 12000000)
+        return 2 if q == 19 and wide else 1
+
     def kernel_label(st):
+        if q == 9:
+            return f"deep_kernel (Q=9, {st}), many steps per launch; figures per step"
+        if steps_per_launch(st) == 2:
+            return f"pair_kernel (Q={q}, {st}), two steps per launch"
         if masked:
             return (f"step_p0_masked_kernel + step_kernel<masked> (Q={q}, {st}), one launch per "
                     "step alternating, averaged over both")
@@ -620,7 +635,8 @@ def main():
 
     def roofline(st, sh, kernel_ms):
         ab = nfluid * 2 * q * STORE_BYTES[st] + (N if masked else 0)
-        achieved = ab / (kernel_ms * 1e-3) / 1e9
+        # a launch of two steps reads and writes each population once, as one of one step does
+        achieved = ab / (steps_per_launch(st) * kernel_ms * 1e-3) / 1e9
         key = f"{args.workload}/{st}{'-shifted' if sh else ''}"
         return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
