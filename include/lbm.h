@@ -162,9 +162,11 @@ lbm_status lbm_get_populations(lbm_lattice* h, double* f_dev);
 
 /* Advance n >= 0 full time steps (collide + stream), enqueued on the lattice's
  * stream.  async.  After the call the stored state is the post-streaming,
- * pre-collision population set at time t0 + n.  Captured into a graph of the
- * caller's, an even n leaves the propagation phase it began in, so that the
- * graph can be replayed. */
+ * pre-collision population set at time t0 + n.  An even n leaves the
+ * propagation phase as it was, an odd n the other one: a caller's own graph of
+ * an even number of captured steps may be replayed whenever an even number of
+ * steps lies between the phase it was captured in and the replay (initialising
+ * the populations counts as step 0). */
 lbm_status lbm_step(lbm_lattice* h, int n);
 
 /* Replay lbm_step in captured HIP graphs of `steps` time steps (even, > 0;

@@ -422,14 +422,14 @@ lbm_status common_phase(lbm_batch* b, int* phase) {
   return LBM_OK;
 }
 
-void advance_views(lbm_batch* b, int n, int phase) {
+void advance_views(lbm_batch* b, int n) {
   for (lbm_lattice* v : b->views) {
-    v->phase = phase;
+    v->phase ^= n & 1;
     v->steps += n;
   }
 }
 
-void launch_pair(lbm_batch* b, bool to_second, bool entry) {
+void launch_pair(lbm_batch* b, bool to_second, bool entry, bool exit) {
   PairBatchLaunch a{};
   a.items = (const PairItem*)(b->aux + b->lay.pair_items_off);
   a.nitems = (int)b->lay.pair.items.size();
@@ -438,45 +438,43 @@ void launch_pair(lbm_batch* b, bool to_second, bool entry) {
   a.src = to_second ? b->pop : b->second;
   a.dst = to_second ? b->second : b->pop;
   a.entry = entry;
+  a.exit = exit;
   a.stream = b->stream;
   // (the plan is empty for 16-bit storage)
   b->storage == LBM_STORE_F64 ? lbm_detail::launch_pair_batch<double>(b->q, b->shifted, a)
                               : lbm_detail::launch_pair_batch<float>(b->q, b->shifted, a);
 }
 
-// Launch n steps from propagation phase `phase`; returns the phase they end
-// in.  Fours of steps run as two passes, there and back (leaving phase 1).
-int launch_steps(lbm_batch* b, int n, int phase, bool passes) {
-  if (passes && b->second) {
-    for (; n >= 4; n -= 4) {
-      launch_pair(b, true, phase == 0);
-      launch_pair(b, false, false);
+// Launch n steps from propagation phase `phase`; they end in the other one
+// after an odd n.  Fours of steps run as two passes, there and back, as those of
+// a single lattice do.
+void launch_steps(lbm_batch* b, int n, int phase) {
+  if (b->second && n >= 4) {
+    if (phase == 0 && n % 4 != 0) {
+      launch_one(b, 0);
       phase = 1;
+      --n;
+    }
+    for (bool first = true; n >= 4; n -= 4, first = false) {
+      launch_pair(b, true, phase == 0 && first, false);
+      launch_pair(b, false, false, phase == 0 && n == 4);
     }
   }
-  for (; n > 0; --n) {
-    launch_one(b, phase);
-    phase ^= 1;
-  }
-  return phase;
+  for (; n > 0; --n, phase ^= 1) launch_one(b, phase);
 }
 
-// Enqueue n steps of every member from propagation phase *phase (graph
-// replays where set up), which is left as the one they end in.  Returns
-// LBM_ERR_HIP on a HIP failure.
-lbm_status enqueue_batch_steps(lbm_batch* b, int n, int* phase) {
+// Enqueue n steps of every member from propagation phase `phase` (graph
+// replays where set up).  Returns LBM_ERR_HIP on a HIP failure.
+lbm_status enqueue_batch_steps(lbm_batch* b, int n, int phase) {
   int left = n;
-  // single steps in a graph that a caller captures: see lbm_step
-  const bool passes = n < 4 || !lbm_detail::captured(b->stream);
   // runs of fewer than eight passes of two steps are launched directly
-  const bool replay = b->graph_steps > 0 && (!b->second || !passes || b->graph_steps >= 16);
+  const bool replay = b->graph_steps > 0 && (!b->second || b->graph_steps >= 16);
   while (replay && left >= b->graph_steps) {
-    hipGraphExec_t& exec = b->graph[*phase];
-    const int end = b->second ? 1 : *phase;  // an even run, through passes or not
+    hipGraphExec_t& exec = b->graph[phase];  // its length is even
     if (!exec) {
       hipGraph_t g = nullptr;
       BHIP_TRY(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-      (void)launch_steps(b, b->graph_steps, *phase, true);
+      launch_steps(b, b->graph_steps, phase);
       hipError_t e = hipStreamEndCapture(b->stream, &g);
       if (e != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -491,9 +489,8 @@ lbm_status enqueue_batch_steps(lbm_batch* b, int n, int* phase) {
     }
     BHIP_TRY(b, hipGraphLaunch(exec, b->stream));
     left -= b->graph_steps;
-    *phase = end;
   }
-  *phase = launch_steps(b, left, *phase, passes);
+  launch_steps(b, left, phase);
   return LBM_OK;
 }
 
@@ -674,7 +671,7 @@ lbm_status lbm_batch_step(lbm_batch* b, int n) {
   int phase = 0;
   st = common_phase(b, &phase);
   if (st) return st;
-  st = enqueue_batch_steps(b, n, &phase);
+  st = enqueue_batch_steps(b, n, phase);
   if (st == LBM_OK) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
@@ -687,7 +684,7 @@ lbm_status lbm_batch_step(lbm_batch* b, int n) {
     drop_batch_graph(b);
     return st;
   }
-  advance_views(b, n, phase);
+  advance_views(b, n);
   return LBM_OK;
 }
 
@@ -727,7 +724,7 @@ lbm_status time_trial(lbm_batch* b, int phase, int trial_steps, std::vector<hipE
   ms[0] /= trial_steps / 2;
   ms[1] /= trial_steps / 2;
   *total = 0.5 * (ms[0] + ms[1]);
-  advance_views(b, trial_steps + 2, phase);
+  advance_views(b, trial_steps + 2);
   return LBM_OK;
 }
 

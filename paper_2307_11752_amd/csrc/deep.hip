@@ -54,7 +54,7 @@ struct DeepGeom {
 template <typename S, bool SHIFT, bool MASKED, int NT, int C>
 __global__ void __launch_bounds__(NT)
     deep_kernel(const S* __restrict__ src, S* __restrict__ dst, const uint32_t* __restrict__ link,
-                const uint32_t* __restrict__ mov, DeepGeom G, int entry,
+                const uint32_t* __restrict__ mov, DeepGeom G, int entry, int exit,
                 StepParams<typename Store<S>::T> p) {
   using T = typename Store<S>::T;
   using U = typename Raw<(int)sizeof(S)>::U;
@@ -169,8 +169,23 @@ __global__ void __launch_bounds__(NT)
   for (int c = 0; c < C; ++c) {
     const int ly = ly0 + c * rows;
     if (ly < k1 || ly >= k1 + G.CY || ty * G.CY + ly - k1 >= G.ny) continue;
+    if (!exit) {
 #pragma unroll
-    for (int i = 0; i < Q; ++i) Store<S>::store(dst + G.pix.at(V::opp[i], own[c]), f[c][i]);
+      for (int i = 0; i < Q; ++i) Store<S>::store(dst + G.pix.at(V::opp[i], own[c]), f[c][i]);
+      continue;
+    }
+    // natural form: into slot i of x + c_i, or, reflected by a wall, slot opp(i) of x
+    if (MASKED && !(lw[c] & LINK_FLUID)) continue;
+    const int y = ty * G.CY + ly - k1;
+    const int X[3] = {xm, x, xp};  // x + c_i by c_i + 1
+    const uint32_t Y[3] = {(uint32_t)G.nx * (uint32_t)(y == 0 ? G.ny - 1 : y - 1), (uint32_t)G.nx * (uint32_t)y,
+                           (uint32_t)G.nx * (uint32_t)(y == G.ny - 1 ? 0 : y + 1)};
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const bool wall = MASKED && i > 0 && ((lw[c] >> (i - 1)) & 1u);
+      const uint32_t away = G.pix.at(i, Y[V::cy[i] + 1] + (uint32_t)X[V::cx[i] + 1]);
+      Store<S>::store(dst + (wall ? G.pix.at(V::opp[i], own[c]) : away), f[c][i]);
+    }
   }
 }
 
@@ -188,7 +203,7 @@ void launch(const DeepLaunch& a, const StepParams<typename Store<Stored>::T>& p)
   G.pix = a.pix;
   hipLaunchKernelGGL((deep_kernel<Stored, SHIFT, MASKED, NT, C>), dim3((unsigned)((G.nblocks + 7) / 8 * 8)),
                      dim3(NT), 0, a.stream, (const Stored*)a.src, (Stored*)a.dst, a.link, a.mov, G,
-                     a.entry, p);
+                     a.entry, a.exit, p);
 }
 
 template <bool SHIFT, bool MASKED>

@@ -28,6 +28,7 @@ struct DeepLaunch {
   const uint32_t* link;
   const uint32_t* mov;
   int entry;  // src in natural form
+  int exit;   // dst in natural form
   hipStream_t stream;
 };
 

@@ -137,10 +137,10 @@ struct lbm_lattice {
   PairPlan pair{};
   DeepPlan deep{};  // D2Q9: many steps per pass (deep.hip), in the same way
   // Replay of captured runs of graph_steps steps (0 = direct launches), one
-  // per propagation phase they start in and parity of their first step.  The
-  // graphs bake in the kernel arguments, so any parameter change drops them.
+  // per propagation phase they start in.  The graphs bake in the kernel
+  // arguments, so any parameter change drops them.
   int graph_steps = 0;
-  hipGraphExec_t graph[4] = {};
+  hipGraphExec_t graph[2] = {};
   // Non-null for a lattice owned by a batch (lbm_batch_lattice): the batch
   // advances it, and calls that would change what the batch launch assumes
   // are refused.
@@ -150,11 +150,6 @@ struct lbm_lattice {
 
 
 namespace lbm_detail {
-// A caller is capturing this stream into a graph of its own.
-inline bool captured(hipStream_t stream) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  return stream && hipStreamIsCapturing(stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
-}
 lbm_status fail(lbm_lattice* h, lbm_status st, const std::string& msg);
 void drop_graph(lbm_lattice* h);
 // lbm_lattice_create with an explicit scratch area: own_scratch bytes of the

@@ -703,7 +703,7 @@ inline bool flat_masked(const lbm_lattice* h) {
 }
 
 template <typename T>
-StepParams<T> make_params(const lbm_lattice* h, long long step) {
+StepParams<T> make_params(const lbm_lattice* h, int parity) {
   StepParams<T> p{};
   p.omega = (T)h->omega;
   p.kguo = (T)(1.0 - 0.5 * h->omega);
@@ -725,8 +725,8 @@ StepParams<T> make_params(const lbm_lattice* h, long long step) {
     uwdot += fabs(cu);
   }
   p.has_moving = (h->has_moving_cells && uwdot != 0.0) ? 1 : 0;
-  // `step`: the number of the (first) step taken since the initialisation
-  if (!h->all_fluid && flat_masked(h)) p.fused_u = (step & 1) ? 2 : 1;
+  // `parity`: of the number of steps taken before the launch's first
+  if (!h->all_fluid && flat_masked(h)) p.fused_u = (parity & 1) ? 2 : 1;
   return p;
 }
 
@@ -778,14 +778,14 @@ struct Ops {
     }
   }
 
-  static void step(lbm_lattice* h, int phase, long long number) {
+  static void step(lbm_lattice* h, int phase) {
     const bool passes = h->pair.use || h->deep.use;
-    sizeof(S) == 2 && !passes ? step_as<sizeof(S) == 2>(h, phase, number) : step_as<false>(h, phase, number);
+    sizeof(S) == 2 && !passes ? step_as<sizeof(S) == 2>(h, phase) : step_as<false>(h, phase);
   }
 
   template <bool FREE>
-  static void step_as(lbm_lattice* h, int phase, long long number) {
-    StepParams<T> p = make_params<T>(h, number);
+  static void step_as(lbm_lattice* h, int phase) {
+    StepParams<T> p = make_params<T>(h, phase);
     p.base = (T)Store<S>::unit;
     S* pop = (S*)h->pop;
     const uint32_t* link = (const uint32_t*)(h->aux + h->lay.link);
@@ -847,22 +847,23 @@ struct Ops {
     }
   }
 
-  // Two steps from src (natural form: entry) to dst.
-  static void deep(lbm_lattice* h, const void* src, void* dst, int steps, bool entry,
-                   long long number) {
-    StepParams<T> p = make_params<T>(h, number);
+  // `steps` steps (pair: two) from src to dst, the first of them after an even
+  // number of steps or, parity 1, an odd one; entry, exit: src, dst in natural form.
+  static void deep(lbm_lattice* h, const void* src, void* dst, int steps, bool entry, bool exit,
+                   int parity) {
+    StepParams<T> p = make_params<T>(h, parity);
     p.base = (T)Store<S>::unit;
     const DeepLaunch a{&h->deep, h->nx, h->ny, h->pix, steps, src, dst,
                        (const uint32_t*)(h->aux + h->lay.link),
-                       (const uint32_t*)(h->aux + h->lay.mov), entry ? 1 : 0, h->stream};
+                       (const uint32_t*)(h->aux + h->lay.mov), entry, exit, h->stream};
     lbm_detail::launch_deep<S>(SHIFT, !h->all_fluid, a, p);
   }
 
-  static void pair(lbm_lattice* h, const void* src, void* dst, bool entry, long long number) {
-    StepParams<T> p = make_params<T>(h, number);
+  static void pair(lbm_lattice* h, const void* src, void* dst, bool entry, bool exit, int parity) {
+    StepParams<T> p = make_params<T>(h, parity);
     p.base = (T)Store<S>::unit;
     const PairLaunch a{&h->pair, src, dst, (const uint32_t*)(h->aux + h->lay.link),
-                       (const uint32_t*)(h->aux + h->lay.mov), entry ? 1 : 0, h->stream};
+                       (const uint32_t*)(h->aux + h->lay.mov), entry, exit, h->stream};
     lbm_detail::launch_pair<S>(SHIFT, !h->all_fluid, a, p);
   }
 
@@ -913,9 +914,9 @@ struct Ops {
 };
 
 struct OpTable {
-  void (*step)(lbm_lattice*, int, long long);
-  void (*pair)(lbm_lattice*, const void*, void*, bool, long long);
-  void (*deep)(lbm_lattice*, const void*, void*, int, bool, long long);
+  void (*step)(lbm_lattice*, int);
+  void (*pair)(lbm_lattice*, const void*, void*, bool, bool, int);
+  void (*deep)(lbm_lattice*, const void*, void*, int, bool, bool, int);
   void (*get_pop)(lbm_lattice*, double*);
   void (*set_pop)(lbm_lattice*, const double*);
   void (*init_eq)(lbm_lattice*, const double*, const double*);
@@ -1033,35 +1034,38 @@ lbm_status reduce_totals(lbm_lattice* h, double* partials, double* result, doubl
   return LBM_OK;
 }
 
-// Launch n steps from propagation phase `phase`, the first of them number
-// `number` since the initialisation; returns the phase they end in.  Where the
-// lattice takes passes, they go there and back between the two population
-// buffers and leave phase 1: D2Q9 an even number of about equal ones from four
-// steps on, D3Q19 two of two steps for every four.  Other steps run one by one
-// in place.
-int launch_steps(lbm_lattice* h, const OpTable& t, int n, int phase, long long number, bool passes) {
-  if (passes && h->deep.use && h->second && n >= 4) {
-    for (int left = (n + 2 * h->deep.steps - 1) / (2 * h->deep.steps) * 2; left > 0; --left) {
-      const int k = (n + left - 1) / left;
-      t.deep(h, left % 2 == 0 ? h->pop : h->second, left % 2 == 0 ? h->second : h->pop, k, phase == 0,
-             number);
-      n -= k;
-      number += k;
-      phase = 1;
+// Launch n steps from propagation phase `phase`; returns the phase they end in,
+// the other one after an odd n: a graph that a caller captured, and the other
+// members of a batch, rely on it.  (So the phase is also the parity of the steps
+// taken since the initialisation.)  Where the lattice takes passes, they go there
+// and back between the two population buffers: D2Q9 an even number of about equal
+// ones from four steps on, D3Q19 two of two steps for every four; other steps
+// run one by one in place, the first of them before the passes where that
+// makes the passes begin in phase 1.  Passes that have to end in phase 0 leave
+// the natural form.
+int launch_steps(lbm_lattice* h, const OpTable& t, int n, int phase) {
+  if (h->deep.use && h->second && n >= 4) {
+    const int end = phase ^ (n & 1);
+    for (int left = (n + 2 * h->deep.steps - 1) / (2 * h->deep.steps) * 2, done = 0; left > 0; --left) {
+      const int k = (n - done + left - 1) / left;
+      t.deep(h, left % 2 == 0 ? h->pop : h->second, left % 2 == 0 ? h->second : h->pop, k,
+             done == 0 && phase == 0, left == 1 && end == 0, (phase + done) & 1);
+      done += k;
     }
-    return phase;
+    return end;
   }
-  if (passes && h->pair.use && h->second) {
-    for (; n >= 4; n -= 4, number += 4) {
-      t.pair(h, h->pop, h->second, phase == 0, number);
-      t.pair(h, h->second, h->pop, false, number + 2);
+  if (h->pair.use && h->second && n >= 4) {
+    if (phase == 0 && n % 4 != 0) {
+      t.step(h, 0);
       phase = 1;
+      --n;
+    }
+    for (bool first = true; n >= 4; n -= 4, first = false) {
+      t.pair(h, h->pop, h->second, phase == 0 && first, false, phase);
+      t.pair(h, h->second, h->pop, false, phase == 0 && n == 4, phase);
     }
   }
-  for (; n > 0; --n, ++number) {
-    t.step(h, phase, number);
-    phase ^= 1;
-  }
+  for (; n > 0; --n, phase ^= 1) t.step(h, phase);
   return phase;
 }
 
@@ -1070,24 +1074,18 @@ int launch_steps(lbm_lattice* h, const OpTable& t, int n, int phase, long long n
 lbm_status enqueue_steps(lbm_lattice* h, int n) {
   const OpTable t = ops(h);
   int left = n;
-  // A caller's own graph is replayed from the phase it was captured in: single
-  // steps, an even number of which returns to it.  (Passes always end in phase 1.)
-  const bool passes = n < 4 || !lbm_detail::captured(h->stream);
   // Runs of fewer than eight passes are launched directly: cut into replays
   // they would be shorter passes, and single steps between them (341^2 BF16
   // cavity over 32 steps: replays of two 366 us, directly 68 us).
-  const int pass = !h->second || !passes ? 0 : (h->deep.use ? h->deep.steps : (h->pair.use ? 2 : 0));
+  const int pass = !h->second ? 0 : (h->deep.use ? h->deep.steps : (h->pair.use ? 2 : 0));
   const bool replay = h->graph_steps > 0 && h->graph_steps >= 8 * pass;
   while (replay && left >= h->graph_steps) {
-    // the phase a run of this length ends in (its length is even: the phase it
-    // starts in, unless it takes passes)
-    const int end = pass ? 1 : h->phase;
-    const long long number = h->steps + (n - left);
-    hipGraphExec_t& exec = h->graph[2 * (number & 1) + h->phase];
+    // the captured run's length is even, so it ends in the phase it starts in
+    hipGraphExec_t& exec = h->graph[h->phase];
     if (!exec) {
       hipGraph_t g = nullptr;
       HIP_TRY(h, hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-      (void)launch_steps(h, t, h->graph_steps, h->phase, number, true);
+      (void)launch_steps(h, t, h->graph_steps, h->phase);
       hipError_t e = hipStreamEndCapture(h->stream, &g);
       if (e != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -1102,9 +1100,8 @@ lbm_status enqueue_steps(lbm_lattice* h, int n) {
     }
     HIP_TRY(h, hipGraphLaunch(exec, h->stream));
     left -= h->graph_steps;
-    h->phase = end;
   }
-  h->phase = launch_steps(h, t, left, h->phase, h->steps + (n - left), passes);
+  h->phase = launch_steps(h, t, left, h->phase);
   return LBM_OK;
 }
 

@@ -28,7 +28,7 @@ using Stored = bf16s;
 // tiles (plane after plane of them), so that neighbouring tiles, which read
 // each other's columns, share one L2.  TGV 256^3 FP32: 487 us a pass against
 // 518 us in plain order (fetched bytes 1.06x the populations).
-template <int Q, typename S, bool SHIFT, bool MASKED, bool SEP, bool SMALL>
+template <int Q, typename S, bool SHIFT, bool MASKED, bool SEP, bool SMALL, bool EXIT>
 __global__ void __launch_bounds__((pair_columns<Q, S, SMALL>()))
     pair_kernel(const S* __restrict__ src, S* __restrict__ dst, const uint32_t* __restrict__ link,
                 const uint32_t* __restrict__ mov, PairGeom G, int entry,
@@ -38,15 +38,15 @@ __global__ void __launch_bounds__((pair_columns<Q, S, SMALL>()))
   if (id >= G.nblocks) return;  // the grid is a multiple of 8
   const int zc = id / G.tiles;
   const int z0 = zc * G.ZC;
-  pair_pass<Q, S, SHIFT, MASKED, SEP, SMALL>(src, dst, link, mov, G, entry != 0, id - zc * G.tiles,
-                                             z0, min(z0 + G.ZC, G.nz), p);
+  pair_pass<Q, S, SHIFT, MASKED, SEP, SMALL, EXIT>(src, dst, link, mov, G, entry != 0,
+                                                   id - zc * G.tiles, z0, min(z0 + G.ZC, G.nz), p);
 }
 
 #if LBM_PAIR_STORAGE <= 1
 // The same pass over a batch: one work-group per item of the work list.  Members
 // differ in the columns of a tile, so waves past an item's last column end at
 // once (a barrier waits for the surviving waves only).
-template <int Q, typename S, bool SHIFT, bool SMALL>
+template <int Q, typename S, bool SHIFT, bool SMALL, bool EXIT>
 __global__ void __launch_bounds__((pair_columns<Q, S, SMALL>()))
     pair_batch_kernel(const S* __restrict__ src, S* __restrict__ dst,
                       const PairItem* __restrict__ items, int entry) {
@@ -57,37 +57,40 @@ __global__ void __launch_bounds__((pair_columns<Q, S, SMALL>()))
   StepParams<typename Store<S>::T> p{};
   p.base = (typename Store<S>::T)Store<S>::unit;
   p.omega = (typename Store<S>::T)it.omega;
-  pair_pass<Q, S, SHIFT, false, false, SMALL>(src + it.pop_off, dst + it.pop_off, nullptr, nullptr,
-                                              G, entry != 0, it.tile, it.z0, it.z1, p);
+  pair_pass<Q, S, SHIFT, false, false, SMALL, EXIT>(src + it.pop_off, dst + it.pop_off, nullptr, nullptr,
+                                                    G, entry != 0, it.tile, it.z0, it.z1, p);
+}
+
+template <int Q, bool SHIFT, bool EXIT>
+void launch_batch(const PairBatchLaunch& a) {
+  const auto kernel = a.small ? pair_batch_kernel<Q, Stored, SHIFT, true, EXIT>
+                              : pair_batch_kernel<Q, Stored, SHIFT, false, EXIT>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)a.nitems), dim3((unsigned)a.threads), 0, a.stream,
+                     (const Stored*)a.src, (Stored*)a.dst, a.items, a.entry);
 }
 
 template <int Q, bool SHIFT>
 void launch_batch(const PairBatchLaunch& a) {
-  const dim3 grid((unsigned)a.nitems), block((unsigned)a.threads);
-  if (a.small)
-    hipLaunchKernelGGL((pair_batch_kernel<Q, Stored, SHIFT, true>), grid, block, 0, a.stream,
-                       (const Stored*)a.src, (Stored*)a.dst, a.items, a.entry);
-  else
-    hipLaunchKernelGGL((pair_batch_kernel<Q, Stored, SHIFT, false>), grid, block, 0, a.stream,
-                       (const Stored*)a.src, (Stored*)a.dst, a.items, a.entry);
+  a.exit ? launch_batch<Q, SHIFT, true>(a) : launch_batch<Q, SHIFT, false>(a);
 }
 #endif
 
-template <bool SHIFT, bool MASKED>
+template <bool SHIFT, bool MASKED, bool EXIT>
 void launch(const PairLaunch& a, const StepParams<typename Store<Stored>::T>& p) {
   const PairGeom& G = a.plan->geom;
   const dim3 grid((unsigned)((G.nblocks + 7) / 8 * 8)), block((unsigned)((G.W * G.H + 63) / 64 * 64));
   const Stored* src = (const Stored*)a.src;
   Stored* dst = (Stored*)a.dst;
-  if (a.plan->small)
-    hipLaunchKernelGGL((pair_kernel<19, Stored, SHIFT, MASKED, false, true>), grid, block, 0,
-                       a.stream, src, dst, a.link, a.mov, G, a.entry, p);
-  else if (MASKED && a.plan->separable)
-    hipLaunchKernelGGL((pair_kernel<19, Stored, SHIFT, MASKED, MASKED, false>), grid, block, 0,
-                       a.stream, src, dst, a.link, a.mov, G, a.entry, p);
-  else
-    hipLaunchKernelGGL((pair_kernel<19, Stored, SHIFT, MASKED, false, false>), grid, block, 0,
-                       a.stream, src, dst, a.link, a.mov, G, a.entry, p);
+  const auto kernel = a.plan->small ? pair_kernel<19, Stored, SHIFT, MASKED, false, true, EXIT>
+                      : MASKED && a.plan->separable
+                          ? pair_kernel<19, Stored, SHIFT, MASKED, MASKED, false, EXIT>
+                          : pair_kernel<19, Stored, SHIFT, MASKED, false, false, EXIT>;
+  hipLaunchKernelGGL(kernel, grid, block, 0, a.stream, src, dst, a.link, a.mov, G, a.entry, p);
+}
+
+template <bool SHIFT, bool MASKED>
+void launch(const PairLaunch& a, const StepParams<typename Store<Stored>::T>& p) {
+  a.exit ? launch<SHIFT, MASKED, true>(a, p) : launch<SHIFT, MASKED, false>(a, p);
 }
 
 }  // namespace

@@ -42,6 +42,7 @@ struct PairLaunch {
   const uint32_t* link;
   const uint32_t* mov;
   int entry;  // src in natural form
+  int exit;   // dst in natural form
   hipStream_t stream;
 };
 
@@ -60,7 +61,7 @@ struct PairBatchLaunch {
   bool small;
   const void* src;
   void* dst;
-  int entry;
+  int entry, exit;
   hipStream_t stream;
 };
 
