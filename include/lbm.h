@@ -96,13 +96,18 @@ typedef enum {
  * lbm_totals and the staging of lbm_moments: 32 bytes per cell, at least
  * 64 KiB and at most 1 MiB), plus, for populations below 2^32 bytes, a second
  * population buffer of pop_bytes, through which runs of four and more steps
- * advance two steps per pass (the state is in dev_pop again when the run
- * ends).  lbm_lattice_create also takes an aux buffer without that last part
- * (9 bytes per cell plus the scratch, each part rounded up to 256 bytes): the
- * lattice then takes every step in place.  The results are the same bit for
- * bit.  Host-only; needs no GPU. */
+ * advance several steps per pass (D3Q19 two; the state is in dev_pop again when
+ * the run ends) and lbm_moments copies large fields.  lbm_lattice_create also
+ * takes an aux buffer without that last part (lbm_min_aux_bytes): the lattice
+ * then takes every step in place.  The results are the same bit for bit.
+ * Host-only; needs no GPU. */
 lbm_status lbm_required_bytes(lbm_descriptor d, int nx, int ny, int nz, lbm_storage s,
                               size_t* pop_bytes, size_t* aux_bytes);
+
+/* The smallest aux buffer lbm_lattice_create takes, without the second
+ * population buffer.  Host-only; needs no GPU. */
+lbm_status lbm_min_aux_bytes(lbm_descriptor d, int nx, int ny, int nz, lbm_storage s,
+                             size_t* aux_bytes);
 
 /* Create a lattice on the current HIP device.  tau is the BGK relaxation time
  * (omega = 1/tau, collision equation of the guide's introduction); it must be
@@ -163,10 +168,9 @@ lbm_status lbm_get_populations(lbm_lattice* h, double* f_dev);
 /* Advance n >= 0 full time steps (collide + stream), enqueued on the lattice's
  * stream.  async.  After the call the stored state is the post-streaming,
  * pre-collision population set at time t0 + n.  An even n leaves the
- * propagation phase as it was, an odd n the other one: a caller's own graph of
- * an even number of captured steps may be replayed whenever an even number of
- * steps lies between the phase it was captured in and the replay (initialising
- * the populations counts as step 0). */
+ * propagation phase as it was, an odd n the other one.  So a caller's own graph of
+ * an even number of captured steps may be replayed wherever the number of steps
+ * since the initialisation is even (odd), if it was when the graph was captured. */
 lbm_status lbm_step(lbm_lattice* h, int n);
 
 /* Replay lbm_step in captured HIP graphs of `steps` time steps (even, > 0;
@@ -243,11 +247,15 @@ lbm_status lbm_lattice_destroy(lbm_lattice* h);
 typedef struct lbm_batch lbm_batch; /* opaque handle */
 
 /* Host-only sizes of the batch's population and aux buffers.  The aux buffer
- * includes the second population buffer of the two-step passes;
- * lbm_batch_create also takes an aux buffer without it (every step then runs
- * alone). */
+ * includes the second population buffer of the two-step passes, where the batch
+ * takes them; lbm_batch_create also takes an aux buffer without it
+ * (lbm_batch_min_aux_bytes): every step then runs alone. */
 lbm_status lbm_batch_required_bytes(lbm_descriptor d, int count, const int* dims, lbm_storage s,
                                     size_t* pop_bytes, size_t* aux_bytes);
+
+/* The smallest aux buffer lbm_batch_create takes.  Host-only. */
+lbm_status lbm_batch_min_aux_bytes(lbm_descriptor d, int count, const int* dims, lbm_storage s,
+                                   size_t* aux_bytes);
 
 /* Create the batch on the current device (sync: uploads the all-fluid
  * geometry of every member).  Arguments as lbm_lattice_create, per member. */

@@ -43,6 +43,7 @@ _PD = ctypes.POINTER(ctypes.c_double)
 
 SIGNATURES = {
     "lbm_required_bytes": ([_I, _I, _I, _I, _I, _PSZ, _PSZ], _I),
+    "lbm_min_aux_bytes": ([_I, _I, _I, _I, _I, _PSZ], _I),
     "lbm_lattice_create": ([_PP, _I, _I, _I, _I, _D, _I, _U, _P, _SZ, _P, _SZ, _P], _I),
     "lbm_validate_geometry": ([_I, _I, _I, _I, _P, _U], _I),
     "lbm_set_geometry": ([_P, _P, _U], _I),
@@ -63,6 +64,7 @@ SIGNATURES = {
     "lbm_status_string": ([_I], ctypes.c_char_p),
     "lbm_last_error": ([_P], ctypes.c_char_p),
     "lbm_batch_required_bytes": ([_I, _I, _P, _I, _PSZ, _PSZ], _I),
+    "lbm_batch_min_aux_bytes": ([_I, _I, _P, _I, _PSZ], _I),
     "lbm_batch_create": ([_PP, _I, _I, _P, _P, _I, _U, _P, _SZ, _P, _SZ, _P], _I),
     "lbm_batch_lattice": ([_P, _I, _PP], _I),
     "lbm_batch_step": ([_P, _I], _I),

@@ -16,7 +16,7 @@ import torch
 
 from . import _lib
 from ._lib import check_batch, load
-from .lattice import _STORAGE, Lattice
+from .lattice import _STORAGE, Lattice, aux_buffer
 
 
 class BatchMember(Lattice):
@@ -43,7 +43,10 @@ class BatchMember(Lattice):
 
 
 class Batch:
-    def __init__(self, descriptor, shapes, taus, storage="f32", shifted=False, stream=None):
+    """second_buffer=False: without the second population buffer, as for ``Lattice``."""
+
+    def __init__(self, descriptor, shapes, taus, storage="f32", shifted=False, stream=None,
+                 second_buffer=True):
         if not torch.cuda.is_available():
             raise RuntimeError("the LBM kernels need a ROCm GPU")
         self.lib = load()
@@ -66,12 +69,15 @@ class Batch:
                                                       ctypes.byref(pop_b), ctypes.byref(aux_b)),
                     None)
         self.pop = torch.empty(pop_b.value, dtype=torch.uint8, device=self.device)
-        self.aux = torch.empty(aux_b.value, dtype=torch.uint8, device=self.device)
+        least = ctypes.c_size_t()
+        check_batch(self.lib.lbm_batch_min_aux_bytes(descriptor, self.count, dims, st,
+                                                     ctypes.byref(least)), None)
+        self.aux = aux_buffer(aux_b.value, least.value, second_buffer, self.device)
         h = ctypes.c_void_p()
         check_batch(self.lib.lbm_batch_create(
             ctypes.byref(h), descriptor, self.count, dims, tau, st,
             _lib.FLAG_SHIFTED if shifted else 0, ctypes.c_void_p(self.pop.data_ptr()),
-            pop_b.value, ctypes.c_void_p(self.aux.data_ptr()), aux_b.value,
+            pop_b.value, ctypes.c_void_p(self.aux.data_ptr()), self.aux.numel(),
             ctypes.c_void_p(self.stream.cuda_stream)), None)
         self.h = h
         self.members = []

@@ -182,9 +182,9 @@ struct BatchLayout {
   size_t pair_items_off = 0, second_off = 0, total_with_second = 0;
 };
 
-// tau: NULL where only the sizes matter
+// tau: NULL where only the sizes matter; passes: plan them and place their buffers
 lbm_status batch_layout(lbm_descriptor d, int count, const int* dims, const double* tau,
-                        lbm_storage s, BatchLayout* L, std::string* why) {
+                        lbm_storage s, BatchLayout* L, std::string* why, bool passes = true) {
   if (count <= 0 || !dims) {
     *why = "count must be positive and dims non-NULL";
     return LBM_ERR_ARG;
@@ -232,7 +232,7 @@ lbm_status batch_layout(lbm_descriptor d, int count, const int* dims, const doub
   L->scratch_off = align256(L->items1_off + sizeof(BatchItem) * items1);
   L->scratch_bytes = scratch_size(max_cells);
   L->aux_total = L->total_with_second = align256(L->scratch_off + L->scratch_bytes);
-  {
+  if (passes) {
     std::vector<PairMember> members;
     for (int b = 0; b < count; ++b) {
       const int nx = dims[3 * b], ny = dims[3 * b + 1], nz = dims[3 * b + 2];
@@ -506,6 +506,16 @@ lbm_status lbm_batch_required_bytes(lbm_descriptor d, int count, const int* dims
   if (st) return lbm_detail::fail(nullptr, st, why);
   if (pop_bytes) *pop_bytes = L.pop_total;
   if (aux_bytes) *aux_bytes = L.total_with_second;
+  return LBM_OK;
+}
+
+lbm_status lbm_batch_min_aux_bytes(lbm_descriptor d, int count, const int* dims, lbm_storage s,
+                                   size_t* aux_bytes) {
+  BatchLayout L;
+  std::string why;
+  lbm_status st = batch_layout(d, count, dims, nullptr, s, &L, &why, false);
+  if (st) return lbm_detail::fail(nullptr, st, why);
+  if (aux_bytes) *aux_bytes = L.aux_total;
   return LBM_OK;
 }
 

@@ -1132,6 +1132,15 @@ lbm_status lbm_required_bytes(lbm_descriptor d, int nx, int ny, int nz, lbm_stor
   return LBM_OK;
 }
 
+lbm_status lbm_min_aux_bytes(lbm_descriptor d, int nx, int ny, int nz, lbm_storage s,
+                             size_t* aux_bytes) {
+  const lbm_status st = lbm_required_bytes(d, nx, ny, nz, s, nullptr, nullptr);
+  if (st) return st;
+  const size_t N = (size_t)nx * ny * nz;
+  if (aux_bytes) *aux_bytes = aux_layout(N, scratch_size(N)).total;
+  return LBM_OK;
+}
+
 lbm_status lbm_validate_geometry(lbm_descriptor d, int nx, int ny, int nz,
                                  const uint8_t* material, unsigned periodic_mask) {
   std::string why;

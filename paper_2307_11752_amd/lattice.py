@@ -27,6 +27,18 @@ def required_bytes(descriptor, nx, ny, nz, storage):
     return pop.value, aux.value
 
 
+def aux_buffer(full, least, second_buffer, device):
+    """Device memory for a handle's aux part: `full` bytes, with the second population
+    buffer, or `least`, without it, where the caller does not want it or the card has
+    no room for it.  The results are the same; runs of four and more steps are slower."""
+    if second_buffer and full > least:
+        try:
+            return torch.empty(full, dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            pass
+    return torch.empty(least, dtype=torch.uint8, device=device)
+
+
 def validate_geometry(descriptor, material, periodic):
     """Host-only geometry check; returns the C status (0 = accepted)."""
     lib = load()
@@ -88,10 +100,12 @@ class Lattice(_Handle):
 
     shape = (nx, ny, nz); populations live in a caller-owned uint8 tensor
     ``self.pop`` of ``lbm_required_bytes`` bytes (placement: see include/lbm.h).
+    second_buffer=False saves the memory of a second population buffer, at the price
+    of slower runs of steps; so does, by itself, a card without room for it.
     """
 
     def __init__(self, descriptor, shape, tau, storage="f32", shifted=False, stream=None,
-                 device=None):
+                 device=None, second_buffer=True):
         if not torch.cuda.is_available():
             raise RuntimeError("the LBM kernels need a ROCm GPU")
         self.lib = load()
@@ -108,13 +122,16 @@ class Lattice(_Handle):
             self.stream = stream if stream is not None else torch.cuda.current_stream()
             pop_b, aux_b = required_bytes(descriptor, self.nx, self.ny, self.nz, storage)
             self.pop = torch.empty(pop_b, dtype=torch.uint8, device=self.device)
-            self.aux = torch.empty(aux_b, dtype=torch.uint8, device=self.device)
+            least = ctypes.c_size_t()
+            check(self.lib.lbm_min_aux_bytes(descriptor, self.nx, self.ny, self.nz,
+                                             _STORAGE.get(storage, storage), ctypes.byref(least)))
+            self.aux = aux_buffer(aux_b, least.value, second_buffer, self.device)
             h = ctypes.c_void_p()
             st = self.lib.lbm_lattice_create(
                 ctypes.byref(h), descriptor, self.nx, self.ny, self.nz, float(tau),
                 _STORAGE.get(storage, storage), _lib.FLAG_SHIFTED if shifted else 0,
                 ctypes.c_void_p(self.pop.data_ptr()), pop_b, ctypes.c_void_p(self.aux.data_ptr()),
-                aux_b, ctypes.c_void_p(self.stream.cuda_stream))
+                self.aux.numel(), ctypes.c_void_p(self.stream.cuda_stream))
             check(st, None)
         self.h = h
 
