@@ -617,7 +617,9 @@ def main():
     def steps_per_launch(st):
         """Steps of the launch that a run of many takes (the library's rule for these
         workloads; D2Q9 passes take a number that depends on the lattice)."""
-        wide = STORE_BYTES[st] > 2 or (N <= 1100000 if masked else N >= 12000000)
+        wave_rows = nx % 4 == 0 and nx <= 256 and (nx // 4) & (nx // 4 - 1) == 0
+        wide = STORE_BYTES[st] > 2 or (N <= 1100000 if masked else
+                                       N >= 12000000 or (N <= 1100000 and not wave_rows))
         return 2 if q == 19 and wide else 1
 
     def kernel_label(st):
@@ -789,7 +791,9 @@ def main():
         "data": "synthetic",
         "config": {"workload": desc, "shape": [nx, ny, nz], "cells": N, "fluid_cells": nfluid,
                    "storage": storage + ("-shifted" if shifted else ""), "tau": wl.tau,
-                   "propagation": "AA in place"},
+                   "propagation": "many steps per pass, two population buffers" if q == 9 else
+                                  "two steps per pass, two population buffers"
+                                  if steps_per_launch(storage) == 2 else "AA in place"},
         "mlups_fluid": round(mlups_fluid, 2),
         "kernel_ms_per_step": round(kernel_ms, 5),
         "roofline": roofline(storage, shifted, kernel_ms),

@@ -296,8 +296,9 @@ lbm_status lbm_batch_get_phase_launch(const lbm_batch* b, int phase, int* thread
  * then time each phase's fastest shape combined, and keep that combination if
  * it beats the fastest common shape, else the common shape (read the result
  * with lbm_batch_get_phase_launch).  Reports phase 1's shape in *threads /
- * *blocks_per_cu and the kept shapes' measured ms per step as
- * *best_ms_per_step (any output may be NULL).
+ * *blocks_per_cu and the kept shapes' measured ms per single step as
+ * *best_ms_per_step (any output may be NULL): a batch that takes two steps per
+ * pass needs less for runs of four and more, to which no shape applies.
  * Members must be initialised (any state will do); every trial (each
  * candidate, and the combination) advances them by trial_steps + 2 steps (the
  * propagation phase is kept), so initialise them again afterwards.  sync. */

@@ -1,10 +1,11 @@
 """Batched ensembles of periodic lattices (C ABI ``lbm_batch_*``).
 
-Each time step advances every member through the batch's own launches (one
-per propagation phase, and per row width class in the second); runs of steps
-are replayed from a captured HIP graph; ``autotune()`` picks each phase's launch
-shape by measurement (``set_phase_launch`` / ``phase_launch`` set and read one
-phase's).  Members are lattice handles: read them with the ``Lattice``
+FP64 and FP32 batches whose members have four planes or more take fours of steps as
+two passes of two; every other step advances the members through the batch's own
+launches (one per propagation phase, and per row width class in the second).  Runs of
+steps are replayed from a captured HIP graph; ``autotune()`` picks each phase's launch
+shape of single steps by measurement (``set_phase_launch`` / ``phase_launch`` set and
+read one phase's).  Members are lattice handles: read them with the ``Lattice``
 calls (``init_equilibrium``, ``moments``, ``totals``, ``get_populations``).
 """
 from __future__ import annotations
@@ -120,8 +121,9 @@ class Batch:
     def autotune(self, trial_steps=20):
         """Measure the built-in launch shapes and keep the fastest of each phase
         (read them with phase_launch).  Returns phase 1's threads and blocks per
-        CU and the tuned ms per step.  Advances every member (initialise the
-        populations again afterwards)."""
+        CU and the tuned ms per single step (runs of four and more steps of FP64 and
+        FP32 batches take passes of two, which no shape applies to).  Advances every
+        member (initialise the populations again afterwards)."""
         t, b, ms = ctypes.c_int(), ctypes.c_int(), ctypes.c_double()
         self._chk(self.lib.lbm_batch_autotune(self.h, int(trial_steps), ctypes.byref(t),
                                               ctypes.byref(b), ctypes.byref(ms)))

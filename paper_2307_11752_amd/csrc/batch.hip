@@ -240,7 +240,8 @@ lbm_status batch_layout(lbm_descriptor d, int count, const int* dims, const doub
       members.push_back({nx, ny, nz, px, pop_index(qof(d), (size_t)px * ny * nz, storage_bytes(s)),
                          L->pop_off[b] / storage_bytes(s), tau && !std::isinf(tau[b]) ? 1.0 / tau[b] : 0.0});
     }
-    L->pair = lbm_detail::make_pair_batch_plan(qof(d), storage_bytes(s), members, 256 /* compute units */);
+    // 256 compute units, the MI355X's: the sizes are host-only, so no device is asked
+    L->pair = lbm_detail::make_pair_batch_plan(qof(d), storage_bytes(s), members, 256);
     if (!L->pair.items.empty()) {
       L->pair_items_off = L->aux_total;
       L->second_off = align256(L->pair_items_off + sizeof(PairItem) * L->pair.items.size());

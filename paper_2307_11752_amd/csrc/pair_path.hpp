@@ -116,10 +116,10 @@ __device__ __forceinline__ void in_register(V& v) {
 //   own cell's slots (only scalar address parts depend on it).
 //   EXIT: dst is left in natural form: step 2 writes what it sends to x + c_i into
 //   slot i there, or, where a wall reflects it, into slot opp(i) of x; cells that
-//   are not fluid send nothing.  Every slot of a fluid cell has one writer.  Its
-//   lines are shared and written in part: 20 steps that end so take 1.5 % longer
-//   (256^3 FP32 5464 against 5385 us) and 2 % (512 x 128 x 128 with walls 3105
-//   against 3042).
+//   are not fluid send nothing.  Every slot of a fluid cell has one writer.  The
+//   lines it writes are shared and written in part: 20 steps that end so, with a
+//   field read, take 1 % longer (256^3 FP32 5386 against 5330 us) and 3 % (512 x
+//   128 x 128 FP32 with walls 3096 against 3014).
 //   SEP: separable placement.
 template <int Q, typename S, bool SHIFT, bool MASKED, bool SEP, bool SMALL, bool EXIT>
 __device__ __forceinline__ void pair_pass(const S* __restrict__ src, S* __restrict__ dst,
